@@ -159,7 +159,8 @@ hipError_t launch_force_reduce(const ITile *tiles, int ntiles, int tile, const S
 // wavefront.  An item is a group against the later tiles [b0, b1) (global
 // tile indices), or the group's own pairs when b0 == b1.
 struct SymItem {
-    int32_t c, g, t0, ng, b0, b1, slot, pad;  // g: group index within the cluster; t0: its first tile
+    int32_t c, g, t0, ng, b0, b1, slot;  // g: group index within the cluster; t0: its first tile
+    int32_t first;  // the cluster's first item (stores its thermostat factor when the sweep drifts)
 };
 // A 64-atom tile: its j-side partials sit at jbase + g for the nj groups
 // before it; its i-side partials are items [item0, item0 + nitems) at lane
@@ -167,21 +168,46 @@ struct SymItem {
 struct SymTile {
     int32_t c, i0, ni, jbase, nj, item0, nitems, p;
 };
+// Wavefronts per item.  With one, an item of a middle-sized cluster is so long
+// (16 us for two j tiles at two tiles per group) that some SIMDs run two while
+// others run one; four share an item's rotations, read the j tile from LDS
+// instead of rotating it, and take the drift into the density sweep.  us per
+// step, one wavefront against four: 4097 atoms 48.1 / 31.0, 6001: 69.0 / 46.5,
+// 15000: 198 / 170 (mixed 186 / 147), 15 x 2057 in baths 87.3 / 68.8.  Groups of
+// eight tiles (large clusters, items enough to fill the chip) would spill at
+// four wavefronts, and gain nothing there.
+constexpr int sym_waves(int ipt) { return ipt == 8 ? 1 : 4; }
 struct SymLaunch {
     const SymItem *items;
     const int32_t *order;
     const SymTile *tiles;
     int nitems, ntiles, ipt;
+    int waves;      // wavefronts per item: 1 or 4
     double *ipart;  // nitems x 4 x 64*IPT
     double *jpart;  // sum(nj) x 3 x 64
 };
+// Drift folded into a density sweep (row sweeps of staged clusters, symmetric
+// sweeps with four wavefronts per item): every workgroup drifts the atoms it
+// loads (r + dt (lambda v + h F)); mode 2 first finishes the previous step's
+// thermostat factor from the cluster's v^2 tile sums (the finalize's order,
+// so the same bits) and the cluster's first workgroup stores it in
+// st[c].lambda for the force epilogue (fused), which applies lambda and the
+// first half-kick and stores the positions.  Clusters in a Langevin bath have
+// their drifted (r, v) stored by the previous force epilogue (or by
+// launch_bath_prep before the run's first step) and are only staged.
+struct Drift {
+    int mode;   // 0: positions as they are; 1: drift with st[c].lambda; 2: new lambda, then drift
+    int local;  // steps completed in this run before this one (ramp index st[c].step + local)
+    int bath;   // clusters in a Langevin bath: 0 none, 1 all, 2 some (the kernel reads each one's kind)
+};
 // stage 0: the sweep (partials); stage 1: reduce + tile finish (density:
 // rho, P, embedding sums; force: F, kick, pair-energy and v^2 sums).  FP64
-// or mixed; (n, m) = (9, 6) and no cutoff only.
-hipError_t launch_sym_density(const SymLaunch &L, const SweepBuffers &B, const PotConst &pc, int precision,
-                              int stage, hipStream_t s);
-hipError_t launch_sym_force(const SymLaunch &L, const SweepBuffers &B, const StepArgs &a, const PotConst &pc,
-                            int precision, int stage, hipStream_t s);
+// or mixed; (n, m) = (9, 6) and no cutoff only.  The folded drift (dr.mode
+// != 0) and the fused epilogue need four wavefronts per item.
+hipError_t launch_sym_density(const SymLaunch &L, const SweepBuffers &B, const StepArgs &a, const Drift &dr,
+                              const PotConst &pc, int precision, int stage, hipStream_t s);
+hipError_t launch_sym_force(const SymLaunch &L, const SweepBuffers &B, const StepArgs &a, int fused, int local,
+                            int bath, const PotConst &pc, int precision, int stage, hipStream_t s);
 
 // Row sweeps for small clusters: one workgroup of 64 * waves threads per
 // tile of at most 64 atoms against every partner of the tile's cluster;
@@ -198,24 +224,10 @@ struct RowLaunch {
     int uni_off, uni_n, uni_ni;  // uni_ni = 0: use the tables
 };
 constexpr int kRowStageMax = 4096;  // clusters up to this size are staged in LDS (128 KiB)
-// Drift folded into the row density sweep of staged clusters (a single
-// cluster or a batch): every workgroup drifts its whole cluster while staging
-// it (r + dt (lambda v + h F)); mode 2 first finishes the previous step's
-// thermostat factor from the cluster's v^2 tile sums (the finalize's order,
-// so the same bits) and the cluster's first tile stores it in st[c].lambda
-// for the force sweep, whose epilogue (fused) applies lambda and the first
-// half-kick and stores the positions.  Clusters in a Langevin bath have
-// their drifted (r, v) stored by the previous force epilogue (or by
-// launch_bath_prep before the run's first step) and are only staged.
-struct RowDrift {
-    int mode;   // 0: positions as they are; 1: drift with st[c].lambda; 2: new lambda, then drift
-    int local;  // steps completed in this run before this one (ramp index st[c].step + local)
-    int bath;   // clusters in a Langevin bath: 0 none, 1 all, 2 some (the kernel reads each one's kind)
-};
 // The drifted position is evaluated as p + (dt lambda) v with p = r + (dt h) F:
 // mode 1 forms p from r and F, mode 2 reads p and v as stored by the previous
 // fused force epilogue (48 bytes per atom), with the same rounding.
-hipError_t launch_row_density(const RowLaunch &L, const SweepBuffers &B, const StepArgs &a, const RowDrift &dr,
+hipError_t launch_row_density(const RowLaunch &L, const SweepBuffers &B, const StepArgs &a, const Drift &dr,
                               const PotConst &pc, int precision, hipStream_t s);
 // fused: per cluster, the Berendsen/NVE epilogue (lambda, both half-kicks,
 // next drift inputs) or the Langevin one (second half-kick of the stored

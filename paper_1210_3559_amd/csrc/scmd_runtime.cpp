@@ -152,7 +152,7 @@ struct scmd_ctx {
     int row_uni_off = 0, row_uni_n = 0, row_uni_ni = 0;  // single-cluster row plan (ni = 0: tables)
     int row_nmax = 0;
     bool sym = false;
-    int sym_ipt = 4, sym_nitems = 0, sym_ntiles = 0;
+    int sym_ipt = 4, sym_waves = 1, sym_nitems = 0, sym_ntiles = 0;
     DevBuf<SymItem> d_sitems;
     DevBuf<int32_t> d_sorder;
     DevBuf<SymTile> d_stiles;
@@ -214,9 +214,13 @@ int fail(scmd_ctx *c, int code, const std::string &msg) {
         return fail(ctx, SCMD_EDEVICE, "internal error");        \
     }
 
-// Batches of staged clusters (all <= kRowStageMax atoms) up to this many
-// unordered pairs per step run on the row sweeps by default.
-constexpr double kRowBatchPairs = 2.5e7;
+// Row sweeps by default: single clusters up to kRowSingleMax atoms, and
+// batches of staged clusters up to kRowBatchPairsLarge unordered pairs per step
+// (kRowBatchPairs when none has more than kRowBatchSmall atoms); build_plan
+// gives the times on both sides.
+constexpr int kRowSingleMax = 3072;
+constexpr double kRowBatchPairs = 2.5e7, kRowBatchPairsLarge = 2.5e6;
+constexpr int kRowBatchSmall = 384;
 constexpr int kRdfMaxBins = 32768;  // LDS histogram of 128 KiB
 
 int64_t ndof_of(int64_t n) {
@@ -394,7 +398,9 @@ int build_sym_plan(scmd_ctx *c, int target) {
             it.ng = std::min(ipt, nt - g * ipt);
             it.b0 = it.b1 = 0;
             it.slot = first;
+            it.first = g == 0;
             items.push_back(it);
+            it.first = 0;
             for (int b = (g + 1) * ipt; b < nt; b += chunk) {
                 SymItem o = it;
                 o.b0 = d.tile0 + b;
@@ -524,24 +530,28 @@ int build_plan(scmd_ctx *c, std::vector<ITile> *tiles_out) {
     {
         int64_t nmax = 0;
         for (int k = 0; k < c->nclusters; ++k) nmax = std::max<int64_t>(nmax, c->offsets[k + 1] - c->offsets[k]);
-        // Library choice (from the autotuner on MI355X, its table committed
-        // with the Python package): symmetric sweeps for batches and for
-        // clusters above 4096 atoms; eight tiles per wavefront (fewest moves
-        // per pair) and fine splitting for large batches and very large
-        // clusters, two tiles in between.
+        // Library choice, from the launch shapes timed on MI355X: row sweeps
+        // for small clusters, symmetric sweeps for the rest.
         const bool allowed = c->neighbour == SCMD_ALLPAIRS && !c->pc.generic;
         const bool batch = c->nclusters > 1;
-        // row sweeps: single clusters up to 4096 atoms, unless a one-sided
-        // launch shape was given
+        // an explicit one-sided launch shape keeps its path
         const bool shape_given = c->tuning.ipt > 0 || c->tuning.waves_i > 0 || c->tuning.waves_j > 0;
         double upairs = 0.0;  // unordered pairs per step
         for (int k = 0; k < c->nclusters; ++k) {
             const double n = (double)(c->offsets[k + 1] - c->offsets[k]);
             upairs += 0.5 * n * (n - 1.0);
         }
-        // row sweeps evaluate every ordered pair but finish a step in two
-        // launches; the symmetric sweeps need enough work to fill the chip
-        const bool row_default = nmax <= 4096 && !shape_given && (!batch || upairs <= kRowBatchPairs);
+        // Row sweeps evaluate every ordered pair but finish a step in two
+        // launches; symmetric ones evaluate half the pairs in four launches
+        // and need enough work to fill the chip.  us per step, row against
+        // symmetric: 3001 atoms 24.1 / 25.1, 3501 atoms 39 / 28; batches 4 x
+        // 2057 36.7 / 30.7, 30 x 500 26.2 / 23.2, but 100 x 300 25.3 / 28.1
+        // (a cluster of few 64-atom tiles wastes lanes and runs mostly in
+        // diagonal items).  Generic exponents have no symmetric form.
+        const bool row_single = nmax <= (c->pc.generic ? kRowStageMax : kRowSingleMax);
+        const bool row_batch = nmax <= kRowStageMax &&
+                               upairs <= (c->pc.generic || nmax <= kRowBatchSmall ? kRowBatchPairs : kRowBatchPairsLarge);
+        const bool row_default = !shape_given && (batch ? row_batch : row_single);
         if (c->neighbour == SCMD_ALLPAIRS && (c->tuning.pairs == 3 || (c->tuning.pairs == 0 && row_default))) {
             c->sym = false;
             c->row = true;
@@ -550,17 +560,27 @@ int build_plan(scmd_ctx *c, std::vector<ITile> *tiles_out) {
         }
         c->sym = allowed && (c->tuning.pairs == 2 || (c->tuning.pairs == 0 && (batch || nmax > 4096)));
         if (c->sym) {
-            int ipt = nmax > 32768 ? 8 : 2;
-            int target = nmax > 32768 ? 8192 : 2048;
+            // Tiles per wavefront group and items per sweep.  More tiles per
+            // group mean fewer moves per pair but fewer, longer items; us per
+            // step at (2 tiles, 1024 items) / (4, 2048) / (8, 8192): 6001
+            // atoms 46.5 / 55.9, 9000: 81.1 / 80.4, 15000: 188 / 170,
+            // 32000: 749 / 678, 48077: - / 1484 / 1408; below 4200 atoms 512
+            // items beat 1024 (4097: 31.0 / 34.6).
+            int ipt = nmax > 32768 ? 8 : nmax > 9000 ? 4 : 2;
+            int target = nmax > 32768 ? 8192 : nmax > 9000 ? 2048 : nmax > 3600 && nmax <= 4200 ? 512 : 1024;
             if (batch) {
-                // about 32k pairs per work item, 512 to 8192 items
-                ipt = upairs >= 2e8 ? 8 : 2;
-                target = 512;
-                while (target < 8192 && target * 32768.0 * 1.5 < upairs) target *= 2;
+                // 4 x 2057 (8.5e6 pairs) 30.7 us at 512 items, 33.7 at 1024;
+                // 15 x 2057 (3.2e7) 70.7 at 1024, 68.8 at 2048; 40 clusters
+                // of 147-6000 (1.1e8) 215.5 at (2, 2048), 212.3 at (4, 1500);
+                // 256 of them (7e8) 1025 at (2, 2048), 963 at (4, 1500), 958
+                // at (8, 8192)
+                ipt = upairs >= 2e8 ? 8 : upairs >= 6e7 ? 4 : 2;
+                target = upairs >= 2e8 ? 8192 : upairs >= 6e7 ? 1500 : upairs >= 1.2e7 ? 2048 : 512;
             }
             if (c->tuning.ipt == 2 || c->tuning.ipt == 4 || c->tuning.ipt == 8) ipt = c->tuning.ipt;
             if (c->tuning.target_items > 0) target = c->tuning.target_items;
             c->sym_ipt = ipt;
+            c->sym_waves = sym_waves(ipt);
             return build_sym_plan(c, target);
         }
     }
@@ -709,9 +729,29 @@ SweepBuffers buffers(scmd_ctx *c) {
     return SweepBuffers{c->rp.p, c->xp.p, c->f.p, c->v.p, c->rho.p, c->d_part.p, c->d_tile_sums.p, c->dpv.p};
 }
 
+// Clusters in a Langevin bath: 0 none, 1 all, 2 some (fixed while a graph
+// exists: thermostat changes drop it).
+int bath_kind(const scmd_ctx *c) {
+    int nb = 0;
+    for (const ClusterDesc &d : c->cdesc) nb += d.kind == SCMD_LANGEVIN;
+    return nb == 0 ? 0 : (nb == c->nclusters ? 1 : 2);
+}
+
+SymLaunch sym_launch(const scmd_ctx *c) {
+    return SymLaunch{c->d_sitems.p,  c->d_sorder.p, c->d_stiles.p, c->sym_nitems, c->sym_ntiles, c->sym_ipt,
+                     c->sym_waves, c->d_ipart.p,  c->d_jpart.p};
+}
+
+// Whether the drift runs inside the density sweep and the kicks in the force
+// epilogue (row sweeps of staged clusters, symmetric sweeps with four
+// wavefronts per item).
+bool folds_drift(const scmd_ctx *c) {
+    return c->natoms > 0 && ((c->row && c->row_nmax <= kRowStageMax) || (c->sym && c->sym_waves == 4));
+}
+
 // One pair sweep (with its profiling events).  energy = 0 lets the force
 // sweep skip the pair energy (steps whose energies nobody reads).  Row
-// sweeps of staged clusters take the drift (drift_mode, local: RowDrift)
+// sweeps of staged clusters take the drift (drift_mode, local: Drift)
 // and the fused force epilogue.
 hipError_t sweep(scmd_ctx *c, bool force, hipStream_t s, bool capturing, int advance, int energy = 1,
                  int drift_mode = 0, int local = 0, int fused = 0) {
@@ -727,20 +767,15 @@ hipError_t sweep(scmd_ctx *c, bool force, hipStream_t s, bool capturing, int adv
     const StepArgs A = step_args(c, advance, energy);
     hipError_t e;
     if (c->sym) {
-        const SymLaunch L{c->d_sitems.p, c->d_sorder.p, c->d_stiles.p, c->sym_nitems, c->sym_ntiles, c->sym_ipt,
-                          c->d_ipart.p, c->d_jpart.p};
-        e = force ? launch_sym_force(L, B, A, c->pc, c->precision, 0, s)
-                  : launch_sym_density(L, B, c->pc, c->precision, 0, s);
+        const SymLaunch L = sym_launch(c);
+        e = force ? launch_sym_force(L, B, A, fused, local, bath_kind(c), c->pc, c->precision, 0, s)
+                  : launch_sym_density(L, B, A, Drift{drift_mode, local, bath_kind(c)}, c->pc, c->precision, 0, s);
     } else if (c->row) {
         const RowLaunch R{c->d_tiles.p, c->d_order.p, c->d_cdesc.p, c->ntiles, c->row_waves, c->row_nmax,
                           c->row_uni_off, c->row_uni_n, c->row_uni_ni};
-        // which clusters are in a Langevin bath (fixed while a graph exists:
-        // thermostat changes drop it)
-        int nb = 0;
-        for (const ClusterDesc &d : c->cdesc) nb += d.kind == SCMD_LANGEVIN;
-        const int bath = nb == 0 ? 0 : (nb == c->nclusters ? 1 : 2);
+        const int bath = bath_kind(c);
         e = force ? launch_row_force(R, B, A, fused, local, bath, c->pc, c->precision, s)
-                  : launch_row_density(R, B, A, RowDrift{drift_mode, local, bath}, c->pc, c->precision, s);
+                  : launch_row_density(R, B, A, Drift{drift_mode, local, bath}, c->pc, c->precision, s);
     } else if (c->neighbour == SCMD_CELLLIST) {
         e = force ? cell_list_force(c->cells, B, A, c->pc, c->precision, s)
                   : cell_list_density(c->cells, B, c->pc, c->precision, s);
@@ -757,23 +792,24 @@ hipError_t sweep(scmd_ctx *c, bool force, hipStream_t s, bool capturing, int adv
     return hipSuccess;
 }
 
-// rho, F, energies at the current positions; advance = 1 also kicks and
-// runs the thermostat (second half of a step).
 // Sweeps and tile finishes of one force evaluation (everything but the
-// per-cluster finalize).
-// checked: this step's drift ran the cell list's check (single cluster).
+// per-cluster finalize); advance = 1 also kicks.  drift_mode, local, fused: see
+// sweep().  checked: this step's drift ran the cell list's check (single
+// cluster).
 hipError_t enqueue_sweeps(scmd_ctx *c, hipStream_t s, bool capturing, int advance, int energy = 1,
-                          bool checked = false) {
+                          bool checked = false, int drift_mode = 0, int local = 0, int fused = 0) {
     hipError_t e;
     const SweepBuffers B = buffers(c);
     const StepArgs A = step_args(c, advance, energy);
-    if (c->sym) {
-        const SymLaunch L{c->d_sitems.p, c->d_sorder.p, c->d_stiles.p, c->sym_nitems, c->sym_ntiles, c->sym_ipt,
-                          c->d_ipart.p, c->d_jpart.p};
-        if ((e = sweep(c, false, s, capturing, advance)) != hipSuccess) return e;
-        if ((e = launch_sym_density(L, B, c->pc, c->precision, 1, s)) != hipSuccess) return e;
-        if ((e = sweep(c, true, s, capturing, advance, energy)) != hipSuccess) return e;
-        return launch_sym_force(L, B, A, c->pc, c->precision, 1, s);
+    if (c->row || c->sym) {
+        const SymLaunch L = sym_launch(c);
+        const int bath = bath_kind(c);
+        if ((e = sweep(c, false, s, capturing, advance, 1, drift_mode, local)) != hipSuccess) return e;
+        if (c->sym && (e = launch_sym_density(L, B, A, Drift{drift_mode, local, bath}, c->pc, c->precision, 1, s)) !=
+                          hipSuccess)
+            return e;
+        if ((e = sweep(c, true, s, capturing, advance, energy, 0, local, fused)) != hipSuccess) return e;
+        return c->sym ? launch_sym_force(L, B, A, fused, local, bath, c->pc, c->precision, 1, s) : hipSuccess;
     }
     if (c->neighbour == SCMD_CELLLIST) {
         if ((e = cell_list_build(c->cells, c->rp.p, checked, s)) != hipSuccess) return e;
@@ -795,6 +831,7 @@ hipError_t enqueue_forces(scmd_ctx *c, hipStream_t s, bool capturing, int advanc
     return launch_finalize(step_args(c, advance), c->d_tile_sums.p, c->nclusters, advance, s);
 }
 
+
 // A run of nsteps velocity-Verlet steps.  Only the last step of a run
 // accumulates the pair energy: the state is read (getters, samples) only
 // after a run.  The step before it carries the sampled profiling events of
@@ -805,15 +842,15 @@ hipError_t enqueue_forces(scmd_ctx *c, hipStream_t s, bool capturing, int advanc
 hipError_t enqueue_run(scmd_ctx *c, hipStream_t s, bool capturing, int64_t nsteps) {
     hipError_t e;
     const StepArgs A = step_args(c, 1);
-    if (c->row && c->row_nmax <= kRowStageMax && c->natoms > 0) {
-        // two launches per step: the density sweep drifts each staged
-        // cluster (after finishing the previous step's thermostat factor),
-        // the force sweep's epilogue kicks and stores the positions.  For a
-        // cluster in a Langevin bath the force epilogue also runs the next
-        // step's bath moves and stores the drifted positions (a per-atom
-        // kernel does so before the first step of the run).
-        bool bath = false;
-        for (const ClusterDesc &d : c->cdesc) bath = bath || d.kind == SCMD_LANGEVIN;
+    if (folds_drift(c)) {
+        // the density sweep drifts the atoms it loads (after finishing the
+        // previous step's thermostat factor), the force epilogue kicks and
+        // stores the positions: two launches per step on the row sweeps, four
+        // on the symmetric ones.  For a cluster in a Langevin bath the force
+        // epilogue also runs the next step's bath moves and stores the
+        // drifted positions (a per-atom kernel does so before the first step
+        // of the run).
+        const bool bath = bath_kind(c) != 0;
         for (int64_t k = 0; k < nsteps; ++k) {
             // the sampled step is the last one without the pair energy
             if (capturing) c->capture_sample = (k == std::max<int64_t>(0, nsteps - 2));
@@ -822,8 +859,7 @@ hipError_t enqueue_run(scmd_ctx *c, hipStream_t s, bool capturing, int64_t nstep
                 (e = launch_bath_prep(A, c->atom_cluster.p, c->rp.p, c->v.p, c->f.p, c->dpv.p, c->natoms, s)) !=
                     hipSuccess)
                 return e;
-            if ((e = sweep(c, false, s, capturing, 1, 1, k == 0 ? 1 : 2, (int)k)) != hipSuccess) return e;
-            if ((e = sweep(c, true, s, capturing, 1, en, 0, (int)k, 1)) != hipSuccess) return e;
+            if ((e = enqueue_sweeps(c, s, capturing, 1, en, false, k == 0 ? 1 : 2, (int)k, 1)) != hipSuccess) return e;
         }
         c->capture_sample = false;
         if (nsteps > 0) return launch_finalize(A, c->d_tile_sums.p, c->nclusters, (int)nsteps, s);

@@ -474,6 +474,199 @@ __device__ inline double cluster_finalize(int c, const FinalizeArgs &o, double *
 }
 
 // ---------------------------------------------------------------------------
+// Drift folded into a density sweep, and the matching force epilogues (row and
+// split symmetric sweeps; see Drift in scmd_internal.h)
+// ---------------------------------------------------------------------------
+struct DriftArgs {
+    int mode, local;
+    int bath;  // clusters in a Langevin bath: 0 none, 1 all, 2 some (read per cluster)
+    const double4 *v, *f;
+    const double2 *dpv;
+    ClusterState *st;
+    const double *tile_sums;
+    const ClusterDesc *cd;
+    double mass_u, dt, h, dth;
+};
+
+// Drifted position p + (dt lambda) v with p = r + (dt h) F (Drift).
+// Mode 1 reads r, v, F (x, y, z) and forms p; mode 2 reads p, v from the
+// three pairs (px, py), (pz, vx), (vy, vz) stored per atom.
+struct PV {
+    double px, py, pz, vx, vy, vz;
+};
+__device__ __forceinline__ double4 xyz(const double4 *__restrict__ p, int a) {
+    const double *q = reinterpret_cast<const double *>(p + a);
+    return make_double4(q[0], q[1], q[2], 0.0);
+}
+__device__ __forceinline__ double pcomp(double r, double f, double dth) {
+#pragma clang fp contract(off)
+    return r + dth * f;
+}
+__device__ __forceinline__ PV pv_from_rvf(const double4 *__restrict__ r, const double4 *__restrict__ v,
+                                          const double4 *__restrict__ f, int a, double dth) {
+    const double4 ra = xyz(r, a), va = xyz(v, a), fa = xyz(f, a);
+    return PV{pcomp(ra.x, fa.x, dth), pcomp(ra.y, fa.y, dth), pcomp(ra.z, fa.z, dth), va.x, va.y, va.z};
+}
+__device__ __forceinline__ PV pv_load(const double2 *__restrict__ d, int a) {
+    const double2 q0 = d[3 * a], q1 = d[3 * a + 1], q2 = d[3 * a + 2];
+    return PV{q0.x, q0.y, q1.x, q1.y, q2.x, q2.y};
+}
+__device__ __forceinline__ double4 drifted(const PV &q, double dtl) {
+#pragma clang fp contract(off)
+    return make_double4(q.px + dtl * q.vx, q.py + dtl * q.vy, q.pz + dtl * q.vz, 0.0);
+}
+
+// Whether cluster c of a launch that drifts is in a Langevin bath.
+__device__ __forceinline__ bool in_bath(int c, const DriftArgs &da) {
+    return da.bath == 1 || (da.bath == 2 && da.cd[c].kind == SCMD_LANGEVIN);
+}
+
+// The thermostat factor of cluster c for a drift (mode 1: as stored; mode 2:
+// the previous step's factor, finished here from the cluster's v^2 tile sums in
+// the finalize's order, and stored by the one workgroup with `writer`).  A
+// cluster in a Langevin bath has its drifted (r, v) stored already: factor 0
+// (the row sweeps take p + 0 v = p).  Whole workgroups of >= 256 threads; sh
+// needs 12 doubles.
+__device__ __forceinline__ double drift_factor(int c, const DriftArgs &da, bool bath, double *sh, bool writer) {
+    if (bath) return 0.0;
+    ClusterState *sc = da.st + c;
+    if (da.mode != 2) return sc->lambda;
+    const ClusterDesc d = da.cd[c];
+    double e0, e1, v2;
+    cluster_totals<true>(d, da.tile_sums, sh, e0, e1, v2);
+    const KinT kt = kinetic_temperature(d, da.mass_u, v2);
+    double tt;
+    const double lam = thermostat_lambda(d, da.dt, kt.T, sc->step + da.local, &tt);
+    if (writer && threadIdx.x == 0) sc->lambda = lam;
+    return lam;
+}
+
+// Drifted position of atom i (indices into the context's arrays) in the
+// symmetric sweeps: r + dt (lambda v + h F) in the drift kernel's order, or in
+// a bath the drifted r stored with dpv.  The row sweeps' p + (dt lambda) v
+// form saves a third of the bytes where every workgroup loads every atom, but
+// rounds twice at the size of r; here each item loads few atoms.
+__device__ __forceinline__ double4 drifted_atom(const double4 *__restrict__ rp, int i, const DriftArgs &da, bool bath,
+                                                double lam) {
+#pragma clang fp contract(off)
+    if (bath) {
+        const double2 q0 = da.dpv[3 * (size_t)i], q1 = da.dpv[3 * (size_t)i + 1];
+        return make_double4(q0.x, q0.y, q1.x, 0.0);
+    }
+    const double4 r = xyz(rp, i), v = xyz(da.v, i), f = xyz(da.f, i);
+    const double vx = lam * v.x + da.h * f.x, vy = lam * v.y + da.h * f.y, vz = lam * v.z + da.h * f.z;
+    return make_double4(r.x + da.dt * vx, r.y + da.dt * vy, r.z + da.dt * vz, 0.0);
+}
+
+// Force epilogue of a step whose drift ran inside the density sweep: the
+// velocity gets the thermostat factor and the first half-kick with the old
+// force (as in the drift kernel), then the second half-kick with the new one;
+// the drifted position r (x, y, z of the density output) is stored.
+template <bool STORE_PV>
+__device__ __forceinline__ void force_atom_fused(int i, double fx, double fy, double fz, double eu, const double4 &r,
+                                                 const double4 &v_old, const double4 &f_old, double lam,
+                                                 const ForceOut &o, const PotConst &pc, double &epair, double &v2) {
+#pragma clang fp contract(off)
+    const double ei = pc.half_eps_an * eu;
+    const double4 fo = f_old;
+    double4 vi = v_old;
+    vi.x = lam * vi.x;
+    vi.y = lam * vi.y;
+    vi.z = lam * vi.z;
+    vi.x = vi.x + o.h * fo.x;
+    vi.y = vi.y + o.h * fo.y;
+    vi.z = vi.z + o.h * fo.z;
+    o.f[i] = make_double4(fx, fy, fz, ei);
+    vi.x = vi.x + o.h * fx;
+    vi.y = vi.y + o.h * fy;
+    vi.z = vi.z + o.h * fz;
+    o.v[i] = vi;
+    o.rp[i] = make_double4(r.x, r.y, r.z, 0.0);
+    if constexpr (STORE_PV) {  // drift inputs of the next step: p = r + (dt h) F, v
+        double2 *d = o.dpv + 3 * (size_t)i;
+        d[0] = make_double2(r.x + o.dth * fx, r.y + o.dth * fy);
+        d[1] = make_double2(r.z + o.dth * fz, vi.x);
+        d[2] = make_double2(vi.y, vi.z);
+    }
+    epair += ei;
+    v2 += vi.x * vi.x + vi.y * vi.y + vi.z * vi.z;
+}
+
+// Langevin epilogue (a cluster in a bath): the stored post-bath velocity gets
+// the second half-kick; then the first half-kick of the next step with the
+// same force and that step's A, O, A (bath.h), whose drifted (r, v) are
+// stored for the next density sweep.  The order of operations is the same as
+// in the drift kernel.
+__device__ __forceinline__ void force_atom_bath(int i, double fx, double fy, double fz, double eu, const double4 &r,
+                                                const double4 &v_bath, const double3 &xi_next, double c2_next,
+                                                const ClusterDesc &d, const ForceOut &o, const PotConst &pc,
+                                                double &epair, double &v2) {
+#pragma clang fp contract(off)
+    const double ei = pc.half_eps_an * eu;
+    double4 vi = v_bath;
+    vi.x = vi.x + o.h * fx;
+    vi.y = vi.y + o.h * fy;
+    vi.z = vi.z + o.h * fz;
+    o.f[i] = make_double4(fx, fy, fz, ei);
+    o.v[i] = vi;
+    o.rp[i] = make_double4(r.x, r.y, r.z, 0.0);
+    epair += ei;
+    v2 += vi.x * vi.x + vi.y * vi.y + vi.z * vi.z;
+    double4 rn = make_double4(r.x, r.y, r.z, 0.0);
+    vi.x = vi.x + o.h * fx;
+    vi.y = vi.y + o.h * fy;
+    vi.z = vi.z + o.h * fz;
+    // this is step st->step + local + 1 of the cluster; prepare the next one
+    bath_drift_xi(d, c2_next, xi_next, o.dt, rn, vi);
+    double2 *q = o.dpv + 3 * (size_t)i;
+    q[0] = make_double2(rn.x, rn.y);
+    q[1] = make_double2(rn.z, vi.x);
+    q[2] = make_double2(vi.y, vi.z);
+}
+
+// What the force epilogues read of their own atom before its sums are known:
+// position and velocity (bath: the post-bath velocity stored with the drifted
+// position), the old force, and in a bath the noise and its amplitude of the
+// next step.
+struct FusedAtom {
+    double4 r, v, f;
+    double3 xi;
+    double c2;
+};
+__device__ __forceinline__ FusedAtom fused_atom_load(int i, int c, bool bath, const double4 *__restrict__ xp,
+                                                     const ForceOut &o) {
+    FusedAtom a;
+    a.r = a.v = a.f = make_double4(0, 0, 0, 0);
+    a.xi = make_double3(0.0, 0.0, 0.0);
+    a.c2 = 0.0;
+    if (o.fused) a.r = xp[i];
+    if (bath) {
+        const double2 *q = o.dpv + 3 * (size_t)i;
+        const double2 q1 = q[1], q2 = q[2];
+        a.v = make_double4(q1.y, q2.x, q2.y, 0.0);
+        const int64_t next = o.st[c].step + o.local + 2;
+        a.xi = bath_noise(o.cd[c].seed, next, i - o.cd[c].off);
+        a.c2 = bath_c2(o.cd[c], next, o.mass_u);
+    } else {
+        a.v = o.v[i];
+        if (o.fused) a.f = o.f[i];
+    }
+    return a;
+}
+
+// Host: the arguments of the folded drift and of the force epilogues.
+inline DriftArgs drift_args(const SweepBuffers &B, const StepArgs &a, const Drift &dr) {
+    return DriftArgs{dr.mode, dr.local, dr.bath, B.v, B.f, B.dpv, a.st, B.tile_sums, a.cd, a.mass_u, a.dt, a.h,
+                     a.dt * a.h};
+}
+// (the fused epilogue stores the drifted positions: rp is the context's
+// writable position array, which the sweeps otherwise only read)
+inline ForceOut fused_force_out(const SweepBuffers &B, const StepArgs &a, int fused, int local, int bath) {
+    return ForceOut{B.f,   B.v,        B.tile_sums, a.h,   a.advance, fused,    a.st, const_cast<double4 *>(B.rp),
+                    B.dpv, a.dt * a.h, a.cd,        local, a.dt,      a.mass_u, bath};
+}
+
+// ---------------------------------------------------------------------------
 // Cell-list check (see CellCheck): per atom, then merged per workgroup.
 // ---------------------------------------------------------------------------
 // Doubles compared as signed 64-bit integers: flip the magnitude bits of

@@ -249,115 +249,11 @@ __device__ __forceinline__ void stage_copy(double4 *lj, const double4 *__restric
     stage_copy<W>(lj, g, n, [] {});
 }
 
-// Drift arguments of the density sweep (see RowDrift).
-struct RowDriftArgs {
-    int mode, local;
-    int bath;  // clusters in a Langevin bath: 0 none, 1 all, 2 some (read per cluster)
-    const double4 *v, *f;
-    const double2 *dpv;
-    ClusterState *st;
-    const double *tile_sums;
-    const ClusterDesc *cd;
-    double mass_u, dt, h, dth;
-};
-
-// Drifted position p + (dt lambda) v with p = r + (dt h) F (RowDrift).
-// Mode 1 reads r, v, F (x, y, z) and forms p; mode 2 reads p, v from the
-// three pairs (px, py), (pz, vx), (vy, vz) stored per atom.
-struct PV {
-    double px, py, pz, vx, vy, vz;
-};
-__device__ __forceinline__ double4 xyz(const double4 *__restrict__ p, int a) {
-    const double *q = reinterpret_cast<const double *>(p + a);
-    return make_double4(q[0], q[1], q[2], 0.0);
-}
-__device__ __forceinline__ double pcomp(double r, double f, double dth) {
-#pragma clang fp contract(off)
-    return r + dth * f;
-}
-__device__ __forceinline__ PV pv_from_rvf(const double4 *__restrict__ r, const double4 *__restrict__ v,
-                                          const double4 *__restrict__ f, int a, double dth) {
-    const double4 ra = xyz(r, a), va = xyz(v, a), fa = xyz(f, a);
-    return PV{pcomp(ra.x, fa.x, dth), pcomp(ra.y, fa.y, dth), pcomp(ra.z, fa.z, dth), va.x, va.y, va.z};
-}
-__device__ __forceinline__ PV pv_load(const double2 *__restrict__ d, int a) {
-    const double2 q0 = d[3 * a], q1 = d[3 * a + 1], q2 = d[3 * a + 2];
-    return PV{q0.x, q0.y, q1.x, q1.y, q2.x, q2.y};
-}
-__device__ __forceinline__ double4 drifted(const PV &q, double dtl) {
-#pragma clang fp contract(off)
-    return make_double4(q.px + dtl * q.vx, q.py + dtl * q.vy, q.pz + dtl * q.vz, 0.0);
-}
-
-// Force epilogue of a step whose drift ran inside the density sweep: the
-// velocity gets the thermostat factor and the first half-kick with the old
-// force (as in the drift kernel), then the second half-kick with the new one;
-// the drifted position r (x, y, z of the density output) is stored.
-__device__ __forceinline__ void force_atom_fused(int i, double fx, double fy, double fz, double eu, const double4 &r,
-                                                 const double4 &v_old, const double4 &f_old, double lam,
-                                                 const ForceOut &o, const PotConst &pc, double &epair, double &v2) {
-#pragma clang fp contract(off)
-    const double ei = pc.half_eps_an * eu;
-    const double4 fo = f_old;
-    double4 vi = v_old;
-    vi.x = lam * vi.x;
-    vi.y = lam * vi.y;
-    vi.z = lam * vi.z;
-    vi.x = vi.x + o.h * fo.x;
-    vi.y = vi.y + o.h * fo.y;
-    vi.z = vi.z + o.h * fo.z;
-    o.f[i] = make_double4(fx, fy, fz, ei);
-    vi.x = vi.x + o.h * fx;
-    vi.y = vi.y + o.h * fy;
-    vi.z = vi.z + o.h * fz;
-    o.v[i] = vi;
-    o.rp[i] = make_double4(r.x, r.y, r.z, 0.0);
-    // drift inputs of the next step: p = r + (dt h) F, v
-    double2 *d = o.dpv + 3 * (size_t)i;
-    d[0] = make_double2(r.x + o.dth * fx, r.y + o.dth * fy);
-    d[1] = make_double2(r.z + o.dth * fz, vi.x);
-    d[2] = make_double2(vi.y, vi.z);
-    epair += ei;
-    v2 += vi.x * vi.x + vi.y * vi.y + vi.z * vi.z;
-}
-
-// Langevin epilogue (a cluster in a bath): the stored post-bath velocity gets
-// the second half-kick; then the first half-kick of the next step with the
-// same force and that step's A, O, A (bath.h), whose drifted (r, v) are
-// stored for the next density sweep.  The order of operations is the same as
-// in the drift kernel.
-__device__ __forceinline__ void force_atom_bath(int i, double fx, double fy, double fz, double eu, const double4 &r,
-                                                const double4 &v_bath, const double3 &xi_next, double c2_next,
-                                                const ClusterDesc &d, const ForceOut &o, const PotConst &pc,
-                                                double &epair, double &v2) {
-#pragma clang fp contract(off)
-    const double ei = pc.half_eps_an * eu;
-    double4 vi = v_bath;
-    vi.x = vi.x + o.h * fx;
-    vi.y = vi.y + o.h * fy;
-    vi.z = vi.z + o.h * fz;
-    o.f[i] = make_double4(fx, fy, fz, ei);
-    o.v[i] = vi;
-    o.rp[i] = make_double4(r.x, r.y, r.z, 0.0);
-    epair += ei;
-    v2 += vi.x * vi.x + vi.y * vi.y + vi.z * vi.z;
-    double4 rn = make_double4(r.x, r.y, r.z, 0.0);
-    vi.x = vi.x + o.h * fx;
-    vi.y = vi.y + o.h * fy;
-    vi.z = vi.z + o.h * fz;
-    // this is step st->step + local + 1 of the cluster; prepare the next one
-    bath_drift_xi(d, c2_next, xi_next, o.dt, rn, vi);
-    double2 *q = o.dpv + 3 * (size_t)i;
-    q[0] = make_double2(rn.x, rn.y);
-    q[1] = make_double2(rn.z, vi.x);
-    q[2] = make_double2(vi.y, vi.z);
-}
-
 // ---------------------------------------------------------------------------
 // Density sweep
 // ---------------------------------------------------------------------------
 template <int W, int PREC, bool GEN, bool STAGE>
-__global__ __launch_bounds__(64 * W) void k_row_density(RowArgs ra, DensityOut o, PotConst pc, RowDriftArgs da) {
+__global__ __launch_bounds__(64 * W) void k_row_density(RowArgs ra, DensityOut o, PotConst pc, DriftArgs da) {
     extern __shared__ double4 lds_row[];
     const RowTile rt = row_tile(ra);
     const RowLayout L = row_layout<W>(rt.i0, rt.ni, rt.off, rt.n);
@@ -387,8 +283,7 @@ __global__ __launch_bounds__(64 * W) void k_row_density(RowArgs ra, DensityOut o
             // forms p.  A cluster in a Langevin bath has its drifted (r, v)
             // stored already (by the previous force epilogue, or before the
             // run's first step): it takes p + 0 v = p.
-            ClusterState *sc = da.st + rt.c;
-            const bool bath = da.bath == 1 || (da.bath == 2 && da.cd[rt.c].kind == SCMD_LANGEVIN);
+            const bool bath = in_bath(rt.c, da);
             const double4 *gv = da.v + rt.off, *gf = da.f + rt.off;
             const double2 *gd = da.dpv + 3 * (size_t)rt.off;
             const bool stored = da.mode == 2 || bath;
@@ -402,22 +297,7 @@ __global__ __launch_bounds__(64 * W) void k_row_density(RowArgs ra, DensityOut o
             if (a2 < rt.n) t2 = load(a2);
             if (a3 < rt.n) t3 = load(a3);
             __shared__ double sh_tot[12];
-            double lam;
-            if (bath) {
-                lam = 0.0;
-            } else if (da.mode == 2) {
-                // finish the previous step's thermostat factor (finalize order)
-                const ClusterDesc d = da.cd[rt.c];
-                double e0, e1, v2;
-                cluster_totals<true>(d, da.tile_sums, sh_tot, e0, e1, v2);
-                const KinT kt = kinetic_temperature(d, da.mass_u, v2);
-                double tt;
-                lam = thermostat_lambda(d, da.dt, kt.T, sc->step + da.local, &tt);
-                if (rt.first && tid == 0) sc->lambda = lam;
-            } else {
-                lam = sc->lambda;
-            }
-            const double dtl = da.dt * lam;
+            const double dtl = da.dt * drift_factor(rt.c, da, bath, sh_tot, rt.first);
             qi = drifted(own, dtl);
             if (a0 < rt.n) lj[a0] = drifted(t0, dtl);
             if (a1 < rt.n) lj[a1] = drifted(t1, dtl);
@@ -528,7 +408,7 @@ __global__ __launch_bounds__(64 * W) void k_row_force(RowArgs ra, const double4 
             force_atom_bath(i, v[0], v[1], v[2], v[3], src[i - rt.off], v_own, xi_next, c2_next, o.cd[rt.c], o, pc,
                             epair, v2);
         else if (o.fused)
-            force_atom_fused(i, v[0], v[1], v[2], v[3], src[i - rt.off], v_own, f_own, o.st[rt.c].lambda, o, pc,
+            force_atom_fused<true>(i, v[0], v[1], v[2], v[3], src[i - rt.off], v_own, f_own, o.st[rt.c].lambda, o, pc,
                              epair, v2);
         else
             force_atom_v(i, v[0], v[1], v[2], v[3], v_own, o, pc, epair, v2);
@@ -553,7 +433,7 @@ hipError_t allow_lds(K kernel, size_t bytes) {
 
 template <int W, int PREC, bool GEN, bool STAGE>
 hipError_t row_launch(bool force, bool energy, const RowLaunch &L, const SweepBuffers &B, const ForceOut &fo,
-                      const RowDriftArgs &da, const PotConst &pc, hipStream_t s) {
+                      const DriftArgs &da, const PotConst &pc, hipStream_t s) {
     const RowArgs ra{L.tiles, L.order, L.cd, L.uni_off, L.uni_n, L.uni_ni};
     hipError_t e;
     if (force) {
@@ -578,7 +458,7 @@ hipError_t row_launch(bool force, bool energy, const RowLaunch &L, const SweepBu
 
 template <int W, bool STAGE>
 hipError_t row_dispatch_ws(bool force, bool energy, const RowLaunch &L, const SweepBuffers &B, const ForceOut &fo,
-                           const RowDriftArgs &da, const PotConst &pc, int precision, hipStream_t s) {
+                           const DriftArgs &da, const PotConst &pc, int precision, hipStream_t s) {
     if (pc.generic) {
         return precision == SCMD_MIXED ? row_launch<W, SCMD_MIXED, true, STAGE>(force, energy, L, B, fo, da, pc, s)
                                        : row_launch<W, SCMD_FP64, true, STAGE>(force, energy, L, B, fo, da, pc, s);
@@ -589,13 +469,13 @@ hipError_t row_dispatch_ws(bool force, bool energy, const RowLaunch &L, const Sw
 
 template <int W>
 hipError_t row_dispatch_w(bool force, bool energy, const RowLaunch &L, const SweepBuffers &B, const ForceOut &fo,
-                          const RowDriftArgs &da, const PotConst &pc, int precision, hipStream_t s) {
+                          const DriftArgs &da, const PotConst &pc, int precision, hipStream_t s) {
     return L.nmax <= kRowStageMax ? row_dispatch_ws<W, true>(force, energy, L, B, fo, da, pc, precision, s)
                                   : row_dispatch_ws<W, false>(force, energy, L, B, fo, da, pc, precision, s);
 }
 
 hipError_t row_dispatch(bool force, bool energy, const RowLaunch &L, const SweepBuffers &B, const ForceOut &fo,
-                        const RowDriftArgs &da, const PotConst &pc, int precision, hipStream_t s) {
+                        const DriftArgs &da, const PotConst &pc, int precision, hipStream_t s) {
     if (L.ntiles <= 0) return hipSuccess;
     // the drift and the fused epilogue need staged clusters
     if ((da.mode != 0 || fo.fused) && L.nmax > kRowStageMax) return hipErrorInvalidValue;
@@ -610,21 +490,16 @@ hipError_t row_dispatch(bool force, bool energy, const RowLaunch &L, const Sweep
 
 }  // namespace
 
-hipError_t launch_row_density(const RowLaunch &L, const SweepBuffers &B, const StepArgs &a, const RowDrift &dr,
+hipError_t launch_row_density(const RowLaunch &L, const SweepBuffers &B, const StepArgs &a, const Drift &dr,
                               const PotConst &pc, int precision, hipStream_t s) {
     const ForceOut fo{};
-    const RowDriftArgs da{dr.mode, dr.local, dr.bath, B.v, B.f, B.dpv, a.st, B.tile_sums, a.cd, a.mass_u, a.dt, a.h,
-                          a.dt * a.h};
-    return row_dispatch(false, true, L, B, fo, da, pc, precision, s);
+    return row_dispatch(false, true, L, B, fo, drift_args(B, a, dr), pc, precision, s);
 }
 
 hipError_t launch_row_force(const RowLaunch &L, const SweepBuffers &B, const StepArgs &a, int fused, int local,
                             int bath, const PotConst &pc, int precision, hipStream_t s) {
-    // the fused epilogue stores the drifted positions (rp is the context's
-    // writable position array; the sweeps otherwise only read it)
-    const ForceOut fo{B.f,  B.v,       B.tile_sums, a.h,  a.advance, fused,    a.st,  const_cast<double4 *>(B.rp),
-                      B.dpv, a.dt * a.h, a.cd,       local, a.dt,      a.mass_u, bath};
-    const RowDriftArgs da{};
+    const ForceOut fo = fused_force_out(B, a, fused, local, bath);
+    const DriftArgs da{};
     return row_dispatch(true, a.energy != 0, L, B, fo, da, pc, precision, s);
 }
 

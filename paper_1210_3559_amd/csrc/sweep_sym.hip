@@ -17,6 +17,11 @@
 // rotations and join the i sums of their tile), a pair inside one tile
 // one-sidedly from both ends.
 //
+// An item is run by NW wavefronts: each takes 64 / NW of the rotations of
+// every j tile (wavefront w starts with the tile already rotated by
+// w 64 / NW), and the wavefronts' sums are added in LDS in wavefront order, so
+// an item's partials are the same size whatever NW is (sym_waves() chooses).
+//
 // Outputs are partial sums: the i side per item, the j side per (group,
 // tile).  The reduce kernels add, for every atom, its group's i-side items in
 // item order and then the j-side partials of every earlier group in group
@@ -45,9 +50,9 @@ struct IGroup {
     int gi[IPT];
 };
 
-template <int IPT>
-__device__ __forceinline__ void load_group(const SymItem &it, const SymTile *__restrict__ tiles,
-                                           const double4 *__restrict__ src, IGroup<IPT> &G) {
+template <int IPT, typename AT>
+__device__ __forceinline__ void load_group(const SymItem &it, const SymTile *__restrict__ tiles, AT &&at,
+                                           IGroup<IPT> &G) {
     const int lane = threadIdx.x & 63;
 #pragma unroll
     for (int p = 0; p < IPT; ++p) {
@@ -58,7 +63,7 @@ __device__ __forceinline__ void load_group(const SymItem &it, const SymTile *__r
             const SymTile t = tiles[it.t0 + p];
             if (lane < t.ni) {
                 G.gi[p] = t.i0 + lane;
-                const double4 q = src[G.gi[p]];
+                const double4 q = at(G.gi[p]);
                 G.x[p] = q.x;
                 G.y[p] = q.y;
                 G.z[p] = q.z;
@@ -107,18 +112,57 @@ __device__ __forceinline__ void sym_force_pair(double dx, double dy, double dz, 
     if constexpr (EN) eu += un;
 }
 
+// The wavefront of the item this thread belongs to (uniform per wavefront).
+template <int NW>
+__device__ __forceinline__ int item_wave() {
+    return NW == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+}
+
+// Sums of Q slices of IPT * 64 doubles over the item's wavefronts, in wavefront
+// order, stored at out[q * IPT * 64 + k].  v(q, p) is this lane's value of
+// slice q, tile p; sh holds 2 * NW * IPT * 64 doubles, free on entry.
+template <int NW, int IPT, int Q, typename V>
+__device__ __forceinline__ void store_item_sums(double *__restrict__ out, double *sh, int wave, V &&v) {
+    const int lane = threadIdx.x & 63;
+    constexpr int S = IPT * 64;
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        if constexpr (NW == 1) {
+#pragma unroll
+            for (int p = 0; p < IPT; ++p) out[q * S + p * 64 + lane] = v(q, p);
+        } else {
+            double *buf = sh + (q & 1) * NW * S;
+#pragma unroll
+            for (int p = 0; p < IPT; ++p) buf[wave * S + p * 64 + lane] = v(q, p);
+            __syncthreads();
+            for (int k = threadIdx.x; k < S; k += 64 * NW) {
+                double t = buf[k];
+#pragma unroll
+                for (int w = 1; w < NW; ++w) t += buf[w * S + k];
+                out[q * S + k] = t;
+            }
+        }
+    }
+}
+
 // EN: accumulate and store the pair energy (u^n); without it (steps whose
 // energies nobody reads) the energy partials are neither summed nor stored.
-template <int IPT, int PREC, bool EN>
-__global__ __launch_bounds__(64) void k_sym_force(const SymItem *__restrict__ items, const int32_t *__restrict__ order,
-                                                  const SymTile *__restrict__ tiles, const double4 *__restrict__ xp,
-                                                  double *__restrict__ ipart, double *__restrict__ jpart,
-                                                  PotConst pc) {
+template <int IPT, int PREC, bool EN, int NW>
+__global__ __launch_bounds__(64 * NW) void k_sym_force(const SymItem *__restrict__ items,
+                                                       const int32_t *__restrict__ order,
+                                                       const SymTile *__restrict__ tiles,
+                                                       const double4 *__restrict__ xp, double *__restrict__ ipart,
+                                                       double *__restrict__ jpart, PotConst pc) {
+    constexpr int RW = 64 / NW;             // rotations per wavefront
+    constexpr int SI = NW * IPT * 64, SJ = NW * 3 * 64;
+    __shared__ double sh[NW == 1 ? 1 : 2 * (SI > SJ ? SI : SJ)];
+    __shared__ double2 jtile[NW == 1 ? 1 : 2 * 256];
     const SymItem it = items[order[blockIdx.x]];
-    const int lane = threadIdx.x & 63;
+    const int lane = threadIdx.x & 63, wave = item_wave<NW>();
+    const int rot0 = wave * RW;
     const float Af = (float)pc.A;
     IGroup<IPT> G;
-    load_group<IPT>(it, tiles, xp, G);
+    load_group<IPT>(it, tiles, [&](int i) { return xp[i]; }, G);
     float cif[IPT];
     double fx[IPT], fy[IPT], fz[IPT], eu[IPT];
 #pragma unroll
@@ -137,6 +181,13 @@ __global__ __launch_bounds__(64) void k_sym_force(const SymItem *__restrict__ it
                 const bool own = G.gi[b] >= 0;  // past the tile's atoms: the j sentinel
                 double xj = own ? G.x[b] : kFar, yj = own ? G.y[b] : kFar, zj = own ? G.z[b] : kFar;
                 double pj = own ? -G.c[b] : 0.0;
+                if constexpr (NW > 1) {
+                    const int from = (lane - rot0) & 63;
+                    xj = __shfl(xj, from, 64);
+                    yj = __shfl(yj, from, 64);
+                    zj = __shfl(zj, from, 64);
+                    pj = __shfl(pj, from, 64);
+                }
                 double gx = 0.0, gy = 0.0, gz = 0.0;
                 // rotation k: lane l meets atom l - k of tile b; k = 0 is the
                 // self pair inside tile b
@@ -161,10 +212,17 @@ __global__ __launch_bounds__(64) void k_sym_force(const SymItem *__restrict__ it
                     gy = ror1(gy);
                     gz = ror1(gz);
                 };
-                step(false);
+                step(NW > 1 && wave != 0);
 #pragma unroll 2
-                for (int k = 1; k < 64; ++k) step(true);
-                // after 64 rotations the j sums are back in their home lanes
+                for (int k = 1; k < RW; ++k) step(true);
+                // the j sums go back to their home lanes (64 rotations bring
+                // them there by themselves)
+                if constexpr (NW > 1) {
+                    const int at = (lane + rot0 + RW) & 63;
+                    gx = __shfl(gx, at, 64);
+                    gy = __shfl(gy, at, 64);
+                    gz = __shfl(gz, at, 64);
+                }
                 fx[b] += gx;
                 fy[b] += gy;
                 fz[b] += gz;
@@ -173,55 +231,95 @@ __global__ __launch_bounds__(64) void k_sym_force(const SymItem *__restrict__ it
 #pragma unroll
         for (int p = 0; p < IPT; ++p) eu[p] += 2.0 * eus[p];
     } else {
+        // NW > 1: the item's wavefronts share the j tile in LDS, every atom
+        // twice, so that the atom lane l meets at rotation k, (l - k) mod 64,
+        // is entry l + 64 - k of both arrays and no index wraps; only the sums
+        // rotate by DPP.  The next tile's atoms travel while one is worked on.
+        const int dst = (lane - rot0 - RW) & 63;  // atom whose sums this lane ends with
+        SymTile t = tiles[it.b0];
+        auto fetch = [&](const SymTile &u) {
+            return lane < u.ni ? xp[u.i0 + lane] : make_double4(kFar, kFar, kFar, 0.0);
+        };
+        auto put = [&](int b, const double4 &q) {
+            double2 *t0 = jtile + (b & 1) * 256;
+            t0[lane] = t0[64 + lane] = make_double2(q.x, q.y);
+            t0[128 + lane] = t0[192 + lane] = make_double2(q.z, q.w);
+        };
+        double4 nxt = make_double4(kFar, kFar, kFar, 0.0);
+        if (wave == 0) nxt = fetch(t);
+        if constexpr (NW > 1) {
+            if (wave == 0) put(it.b0, nxt);
+            __syncthreads();
+        }
         for (int b = it.b0; b < it.b1; ++b) {
-            const SymTile t = tiles[b];
-            double xj = kFar, yj = kFar, zj = kFar, pj = 0.0;
-            if (lane < t.ni) {
-                const double4 q = xp[t.i0 + lane];
-                xj = q.x;
-                yj = q.y;
-                zj = q.z;
-                pj = q.w;
+            double xj = nxt.x, yj = nxt.y, zj = nxt.z, pj = nxt.w;
+            const int jslot = t.jbase + it.g;
+            if (b + 1 < it.b1) {
+                t = tiles[b + 1];
+                if (wave == 0) nxt = fetch(t);
             }
+            const double2 *jt = jtile + (NW > 1 ? (b & 1) * 256 + lane + 64 - rot0 : 0);
             double gx = 0.0, gy = 0.0, gz = 0.0;
 #pragma unroll 2
-            for (int k = 0; k < 64; ++k) {
+            for (int k = 0; k < RW; ++k) {
+                if constexpr (NW > 1) {
+                    const double2 q0 = jt[-k], q1 = jt[128 - k];
+                    xj = q0.x;
+                    yj = q0.y;
+                    zj = q1.x;
+                    pj = q1.y;
+                }
                 const float pjf = (float)pj;
 #pragma unroll
                 for (int p = 0; p < IPT; ++p) {
                     sym_force_pair<PREC, EN>(G.x[p] - xj, G.y[p] - yj, G.z[p] - zj, G.c[p], pj, cif[p], pjf, fx[p], fy[p],
                                          fz[p], eu[p], gx, gy, gz, pc, Af);
                 }
-                xj = ror1(xj);
-                yj = ror1(yj);
-                zj = ror1(zj);
-                pj = ror1(pj);
+                if constexpr (NW == 1) {
+                    xj = ror1(xj);
+                    yj = ror1(yj);
+                    zj = ror1(zj);
+                    pj = ror1(pj);
+                }
                 gx = ror1(gx);
                 gy = ror1(gy);
                 gz = ror1(gz);
             }
             double ge = 0.0;
             unscale_force<PREC, false>(gx, gy, gz, ge);
-            double *out = jpart + ((size_t)(t.jbase + it.g) * 3) * 64 + lane;
-            out[0] = gx;
-            out[64] = gy;
-            out[128] = gz;
+            double *out = jpart + (size_t)jslot * 3 * 64;
+            if constexpr (NW == 1) {
+                out[lane] = gx;
+                out[64 + lane] = gy;
+                out[128 + lane] = gz;
+            } else {
+                // two buffers in turn: a wavefront reaches this one again only
+                // past the next tile's barrier, when all have read it
+                double *buf = sh + (b & 1) * SJ;
+                buf[wave * 192 + dst] = gx;
+                buf[wave * 192 + 64 + dst] = gy;
+                buf[wave * 192 + 128 + dst] = gz;
+                if (wave == 0 && b + 1 < it.b1) put(b + 1, nxt);
+                __syncthreads();
+                if (threadIdx.x < 192) {
+                    double v = buf[threadIdx.x];
+#pragma unroll
+                    for (int w = 1; w < NW; ++w) v += buf[w * 192 + threadIdx.x];
+                    out[threadIdx.x] = v;
+                }
+            }
         }
 #pragma unroll
         for (int p = 0; p < IPT; ++p) eu[p] *= 2.0;  // each unordered pair once
+        if constexpr (NW > 1) __syncthreads();
     }
 #pragma unroll
     for (int p = 0; p < IPT; ++p) unscale_force<PREC, false>(fx[p], fy[p], fz[p], eu[p]);
-    double *out = ipart + (size_t)it.slot * 4 * 64 * IPT;
-#pragma unroll
-    for (int p = 0; p < IPT; ++p) {
-        out[(0 * IPT + p) * 64 + lane] = fx[p];
-        out[(1 * IPT + p) * 64 + lane] = fy[p];
-        out[(2 * IPT + p) * 64 + lane] = fz[p];
-        // steps without the pair energy leave its slot unwritten (the reduce
-        // of such a step does not read it)
-        if constexpr (EN) out[(3 * IPT + p) * 64 + lane] = eu[p];
-    }
+    // steps without the pair energy leave its slot unwritten (the reduce of
+    // such a step does not read it)
+    store_item_sums<NW, IPT, EN ? 4 : 3>(ipart + (size_t)it.slot * 4 * 64 * IPT, sh, wave, [&](int q, int p) {
+        return q == 0 ? fx[p] : q == 1 ? fy[p] : q == 2 ? fz[p] : eu[p];
+    });
 }
 
 // ---------------------------------------------------------------------------
@@ -239,16 +337,39 @@ __device__ __forceinline__ double sym_density_term(double dx, double dy, double 
     }
 }
 
-template <int IPT, int PREC>
-__global__ __launch_bounds__(64) void k_sym_density(const SymItem *__restrict__ items,
-                                                    const int32_t *__restrict__ order,
-                                                    const SymTile *__restrict__ tiles, const double4 *__restrict__ rp,
-                                                    double *__restrict__ ipart, double *__restrict__ jpart,
-                                                    PotConst pc) {
+// With four wavefronts the sweep can also drift the atoms it loads
+// (da.mode != 0, see Drift): every item finishes its cluster's thermostat
+// factor for itself, and the cluster's first item stores it.
+template <int IPT, int PREC, int NW>
+__global__ __launch_bounds__(64 * NW) void k_sym_density(const SymItem *__restrict__ items,
+                                                         const int32_t *__restrict__ order,
+                                                         const SymTile *__restrict__ tiles,
+                                                         const double4 *__restrict__ rp, double *__restrict__ ipart,
+                                                         double *__restrict__ jpart, DriftArgs da) {
+    constexpr int RW = 64 / NW;
+    constexpr int SI = NW * IPT * 64;
+    __shared__ double sh[NW == 1 ? 1 : 2 * SI];
+    __shared__ double jtile[NW == 1 ? 1 : 2 * 384];
     const SymItem it = items[order[blockIdx.x]];
-    const int lane = threadIdx.x & 63;
+    const int lane = threadIdx.x & 63, wave = item_wave<NW>();
+    const int rot0 = wave * RW;
+    double lam = 1.0;
+    bool bath = false;
+    if constexpr (NW > 1) {
+        if (da.mode != 0) {
+            __shared__ double sh_tot[12];
+            bath = in_bath(it.c, da);
+            lam = drift_factor(it.c, da, bath, sh_tot, it.first != 0);
+        }
+    }
+    auto position = [&](int i) {
+        if constexpr (NW > 1) {
+            if (da.mode != 0) return drifted_atom(rp, i, da, bath, lam);
+        }
+        return rp[i];
+    };
     IGroup<IPT> G;
-    load_group<IPT>(it, tiles, rp, G);
+    load_group<IPT>(it, tiles, position, G);
     double acc[IPT];
 #pragma unroll
     for (int p = 0; p < IPT; ++p) acc[p] = 0.0;
@@ -259,6 +380,12 @@ __global__ __launch_bounds__(64) void k_sym_density(const SymItem *__restrict__ 
             if (b < it.ng) {
                 const bool own = G.gi[b] >= 0;
                 double xj = own ? G.x[b] : kFar, yj = own ? G.y[b] : kFar, zj = own ? G.z[b] : kFar;
+                if constexpr (NW > 1) {
+                    const int from = (lane - rot0) & 63;
+                    xj = __shfl(xj, from, 64);
+                    yj = __shfl(yj, from, 64);
+                    zj = __shfl(zj, from, 64);
+                }
                 double rj = 0.0;
                 auto step = [&](bool with_own_tile) {
 #pragma unroll
@@ -276,42 +403,79 @@ __global__ __launch_bounds__(64) void k_sym_density(const SymItem *__restrict__ 
                     zj = ror1(zj);
                     rj = ror1(rj);
                 };
-                step(false);
+                step(NW > 1 && wave != 0);
 #pragma unroll 2
-                for (int k = 1; k < 64; ++k) step(true);
+                for (int k = 1; k < RW; ++k) step(true);
+                if constexpr (NW > 1) rj = __shfl(rj, (lane + rot0 + RW) & 63, 64);
                 acc[b] += rj;
             }
         }
     } else {
+        // the j tile in LDS as in the force sweep
+        const int dst = (lane - rot0 - RW) & 63;
+        SymTile t = tiles[it.b0];
+        auto fetch = [&](const SymTile &u) {
+            return lane < u.ni ? position(u.i0 + lane) : make_double4(kFar, kFar, kFar, 0.0);
+        };
+        auto put = [&](int b, const double4 &q) {
+            double *t0 = jtile + (b & 1) * 384;
+            t0[lane] = t0[64 + lane] = q.x;
+            t0[128 + lane] = t0[192 + lane] = q.y;
+            t0[256 + lane] = t0[320 + lane] = q.z;
+        };
+        double4 nxt = make_double4(kFar, kFar, kFar, 0.0);
+        if (wave == 0) nxt = fetch(t);
+        if constexpr (NW > 1) {
+            if (wave == 0) put(it.b0, nxt);
+            __syncthreads();
+        }
         for (int b = it.b0; b < it.b1; ++b) {
-            const SymTile t = tiles[b];
-            double xj = kFar, yj = kFar, zj = kFar;
-            if (lane < t.ni) {
-                const double4 q = rp[t.i0 + lane];
-                xj = q.x;
-                yj = q.y;
-                zj = q.z;
+            double xj = nxt.x, yj = nxt.y, zj = nxt.z;
+            const int jslot = t.jbase + it.g;
+            if (b + 1 < it.b1) {
+                t = tiles[b + 1];
+                if (wave == 0) nxt = fetch(t);
             }
+            const double *jt = jtile + (NW > 1 ? (b & 1) * 384 + lane + 64 - rot0 : 0);
             double rj = 0.0;
 #pragma unroll 2
-            for (int k = 0; k < 64; ++k) {
+            for (int k = 0; k < RW; ++k) {
+                if constexpr (NW > 1) {
+                    xj = jt[-k];
+                    yj = jt[128 - k];
+                    zj = jt[256 - k];
+                }
 #pragma unroll
                 for (int p = 0; p < IPT; ++p) {
                     const double t6 = sym_density_term<PREC>(G.x[p] - xj, G.y[p] - yj, G.z[p] - zj);
                     acc[p] += t6;
                     rj += t6;
                 }
-                xj = ror1(xj);
-                yj = ror1(yj);
-                zj = ror1(zj);
+                if constexpr (NW == 1) {
+                    xj = ror1(xj);
+                    yj = ror1(yj);
+                    zj = ror1(zj);
+                }
                 rj = ror1(rj);
             }
-            jpart[(size_t)(t.jbase + it.g) * 64 + lane] = rj;
-        }
-    }
-    double *out = ipart + (size_t)it.slot * 64 * IPT;
+            if constexpr (NW == 1) {
+                jpart[(size_t)jslot * 64 + lane] = rj;
+            } else {
+                double *buf = sh + (b & 1) * NW * 64;
+                buf[wave * 64 + dst] = rj;
+                if (wave == 0 && b + 1 < it.b1) put(b + 1, nxt);
+                __syncthreads();
+                if (threadIdx.x < 64) {
+                    double v = buf[threadIdx.x];
 #pragma unroll
-    for (int p = 0; p < IPT; ++p) out[p * 64 + lane] = acc[p];
+                    for (int w = 1; w < NW; ++w) v += buf[w * 64 + threadIdx.x];
+                    jpart[(size_t)jslot * 64 + threadIdx.x] = v;
+                }
+            }
+        }
+        if constexpr (NW > 1) __syncthreads();
+    }
+    store_item_sums<NW, IPT, 1>(ipart + (size_t)it.slot * 64 * IPT, sh, wave, [&](int, int p) { return acc[p]; });
 }
 
 // ---------------------------------------------------------------------------
@@ -364,64 +528,91 @@ template <int IPT>
 __global__ __launch_bounds__(kSymRed) void k_sym_density_reduce(const SymTile *__restrict__ tiles,
                                                                 const double *__restrict__ ipart,
                                                                 const double *__restrict__ jpart, DensityOut o,
-                                                                PotConst pc) {
+                                                                PotConst pc, DriftArgs da) {
     __shared__ double sh[kSymRedGroups * 64];
-    __shared__ double sh_red[kSymRed];
     const SymTile t = tiles[blockIdx.x];
+    // the atom's position, as the sweep had it, is fetched ahead of the sums
+    double4 q = make_double4(0, 0, 0, 0);
+    if (threadIdx.x < t.ni) {
+        const int i = t.i0 + threadIdx.x;
+        if (da.mode != 0) {
+            const bool bath = in_bath(t.c, da);
+            q = drifted_atom(o.rp, i, da, bath, da.st[t.c].lambda);
+        } else {
+            q = o.rp[i];
+        }
+    }
     sym_sums<IPT, 1, false>(t, ipart, jpart, sh);
+    if (threadIdx.x >= 64) return;
     double emb = 0.0;
-    if (threadIdx.x < t.ni) emb = density_atom(t.i0 + threadIdx.x, sh[threadIdx.x], o, pc);
-    emb = block_sum<kSymRed>(emb, sh_red);
+    if (threadIdx.x < t.ni) emb = density_atom_at(t.i0 + threadIdx.x, sh[threadIdx.x], q, o, pc);
+    emb = wave_total(emb);
     if (threadIdx.x == 0) o.tile_sums[(size_t)blockIdx.x * kTileSums + 0] = emb;
 }
 
 template <int IPT, bool EN>
 __global__ __launch_bounds__(kSymRed) void k_sym_force_reduce(const SymTile *__restrict__ tiles,
                                                               const double *__restrict__ ipart,
-                                                              const double *__restrict__ jpart, ForceOut o,
+                                                              const double *__restrict__ jpart,
+                                                              const double4 *__restrict__ xp, ForceOut o,
                                                               PotConst pc) {
     __shared__ double sh[kSymRedGroups * 4 * 64];
-    __shared__ double sh_red[kSymRed];
     const SymTile t = tiles[blockIdx.x];
-    sym_sums<IPT, 4, EN>(t, ipart, jpart, sh);
-    double epair = 0.0, v2 = 0.0;
     const int l = threadIdx.x;
-    if (l < t.ni) force_atom(t.i0 + l, sh[l], sh[64 + l], sh[128 + l], sh[192 + l], o, pc, epair, v2);
-    epair = block_sum<kSymRed>(epair, sh_red);
-    v2 = block_sum<kSymRed>(v2, sh_red);
-    if (threadIdx.x == 0) {
+    const int i = t.i0 + l;
+    // the epilogue's own-atom loads and, in a bath, the next step's noise do
+    // not depend on the sums: they are issued ahead of them
+    const bool bath = o.fused && (o.bath == 1 || (o.bath == 2 && o.cd[t.c].kind == SCMD_LANGEVIN));
+    FusedAtom a;
+    if (l < t.ni) a = fused_atom_load(i, t.c, bath, xp, o);
+    sym_sums<IPT, 4, EN>(t, ipart, jpart, sh);
+    if (l >= 64) return;
+    double epair = 0.0, v2 = 0.0;
+    if (l < t.ni) {
+        const double fx = sh[l], fy = sh[64 + l], fz = sh[128 + l], eu = sh[192 + l];
+        if (bath)
+            force_atom_bath(i, fx, fy, fz, eu, a.r, a.v, a.xi, a.c2, o.cd[t.c], o, pc, epair, v2);
+        else if (o.fused)
+            force_atom_fused<false>(i, fx, fy, fz, eu, a.r, a.v, a.f, o.st[t.c].lambda, o, pc, epair, v2);
+        else
+            force_atom_v(i, fx, fy, fz, eu, a.v, o, pc, epair, v2);
+    }
+    epair = wave_total(epair);
+    v2 = wave_total(v2);
+    if (l == 0) {
         o.tile_sums[(size_t)blockIdx.x * kTileSums + 1] = epair;
         o.tile_sums[(size_t)blockIdx.x * kTileSums + 2] = v2;
     }
 }
 
-template <int IPT, int PREC>
+template <int IPT, int PREC, int NW>
 hipError_t launch_ipt(bool force, int stage, bool energy, const SymLaunch &L, const SweepBuffers &B,
-                      const ForceOut &fo, const PotConst &pc, hipStream_t s) {
+                      const ForceOut &fo, const DriftArgs &da, const PotConst &pc, hipStream_t s) {
     (void)hipGetLastError();
+    const dim3 block(64 * NW);
     if (stage == 0 && L.nitems > 0) {
         if (force && energy)
-            hipLaunchKernelGGL((k_sym_force<IPT, PREC, true>), dim3(L.nitems), dim3(64), 0, s, L.items, L.order,
+            hipLaunchKernelGGL((k_sym_force<IPT, PREC, true, NW>), dim3(L.nitems), block, 0, s, L.items, L.order,
                                L.tiles, B.xp, L.ipart, L.jpart, pc);
         else if (force)
-            hipLaunchKernelGGL((k_sym_force<IPT, PREC, false>), dim3(L.nitems), dim3(64), 0, s, L.items, L.order,
+            hipLaunchKernelGGL((k_sym_force<IPT, PREC, false, NW>), dim3(L.nitems), block, 0, s, L.items, L.order,
                                L.tiles, B.xp, L.ipart, L.jpart, pc);
         else
-            hipLaunchKernelGGL((k_sym_density<IPT, PREC>), dim3(L.nitems), dim3(64), 0, s, L.items, L.order, L.tiles,
-                               B.rp, L.ipart, L.jpart, pc);
+            hipLaunchKernelGGL((k_sym_density<IPT, PREC, NW>), dim3(L.nitems), block, 0, s, L.items, L.order, L.tiles,
+                               B.rp, L.ipart, L.jpart, da);
     }
     if (stage == 1 && L.ntiles > 0) {
         if (force) {
             if (energy)
                 hipLaunchKernelGGL((k_sym_force_reduce<IPT, true>), dim3(L.ntiles), dim3(kSymRed), 0, s, L.tiles,
-                                   L.ipart, L.jpart, fo, pc);
+                                   L.ipart, L.jpart, B.xp, fo, pc);
             else
                 hipLaunchKernelGGL((k_sym_force_reduce<IPT, false>), dim3(L.ntiles), dim3(kSymRed), 0, s, L.tiles,
-                                   L.ipart, L.jpart, fo, pc);
+                                   L.ipart, L.jpart, B.xp, fo, pc);
         } else {
             const DensityOut o{B.rp, B.xp, B.rho, B.tile_sums};
             hipLaunchKernelGGL((k_sym_density_reduce<IPT>), dim3(L.ntiles), dim3(kSymRed), 0, s, L.tiles, L.ipart,
-                               L.jpart, o, pc);
+                               L.jpart, o, pc, da);
         }
     }
     return hipGetLastError();
@@ -429,31 +620,37 @@ hipError_t launch_ipt(bool force, int stage, bool energy, const SymLaunch &L, co
 
 template <int PREC>
 hipError_t dispatch_ipt(bool force, int stage, bool energy, const SymLaunch &L, const SweepBuffers &B,
-                        const ForceOut &fo, const PotConst &pc, hipStream_t s) {
+                        const ForceOut &fo, const DriftArgs &da, const PotConst &pc, hipStream_t s) {
+#define SCMD_SYM(I, W) launch_ipt<I, PREC, W>(force, stage, energy, L, B, fo, da, pc, s)
+    // the folded drift needs the workgroup-wide totals of four wavefronts
+    if (L.waves != sym_waves(L.ipt) || (L.waves == 1 && (da.mode != 0 || fo.fused))) return hipErrorInvalidValue;
     switch (L.ipt) {
-        case 2: return launch_ipt<2, PREC>(force, stage, energy, L, B, fo, pc, s);
-        case 4: return launch_ipt<4, PREC>(force, stage, energy, L, B, fo, pc, s);
-        case 8: return launch_ipt<8, PREC>(force, stage, energy, L, B, fo, pc, s);
+        case 2: return SCMD_SYM(2, 4);
+        case 4: return SCMD_SYM(4, 4);
+        case 8: return SCMD_SYM(8, 1);
         default: return hipErrorInvalidValue;
     }
+#undef SCMD_SYM
 }
 
 }  // namespace
 
-hipError_t launch_sym_density(const SymLaunch &L, const SweepBuffers &B, const PotConst &pc, int precision,
-                              int stage, hipStream_t s) {
+hipError_t launch_sym_density(const SymLaunch &L, const SweepBuffers &B, const StepArgs &a, const Drift &dr,
+                              const PotConst &pc, int precision, int stage, hipStream_t s) {
     if (pc.generic || pc.cut) return hipErrorInvalidValue;
-    return precision == SCMD_FP64 ? dispatch_ipt<SCMD_FP64>(false, stage, true, L, B, ForceOut{}, pc, s)
-                                  : dispatch_ipt<SCMD_MIXED>(false, stage, true, L, B, ForceOut{}, pc, s);
+    const DriftArgs da = drift_args(B, a, dr);
+    return precision == SCMD_FP64 ? dispatch_ipt<SCMD_FP64>(false, stage, true, L, B, ForceOut{}, da, pc, s)
+                                  : dispatch_ipt<SCMD_MIXED>(false, stage, true, L, B, ForceOut{}, da, pc, s);
 }
 
-hipError_t launch_sym_force(const SymLaunch &L, const SweepBuffers &B, const StepArgs &a, const PotConst &pc,
-                            int precision, int stage, hipStream_t s) {
+hipError_t launch_sym_force(const SymLaunch &L, const SweepBuffers &B, const StepArgs &a, int fused, int local,
+                            int bath, const PotConst &pc, int precision, int stage, hipStream_t s) {
     if (pc.generic || pc.cut) return hipErrorInvalidValue;
-    const ForceOut fo{B.f, B.v, B.tile_sums, a.h, a.advance};
+    const ForceOut fo = fused_force_out(B, a, fused, local, bath);
     const bool energy = a.energy != 0;
-    return precision == SCMD_FP64 ? dispatch_ipt<SCMD_FP64>(true, stage, energy, L, B, fo, pc, s)
-                                  : dispatch_ipt<SCMD_MIXED>(true, stage, energy, L, B, fo, pc, s);
+    return precision == SCMD_FP64
+               ? dispatch_ipt<SCMD_FP64>(true, stage, energy, L, B, fo, DriftArgs{}, pc, s)
+               : dispatch_ipt<SCMD_MIXED>(true, stage, energy, L, B, fo, DriftArgs{}, pc, s);
 }
 
 }  // namespace scmd
