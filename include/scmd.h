@@ -249,7 +249,8 @@ int scmd_compute(scmd_ctx *ctx);
  * all pairs, integrated with velocity-Verlet; forces at the initial
  * positions are computed first if needed).  Steps are replayed from captured
  * HIP graphs: a 32-step graph and a graph of the remainder (nsteps mod 32),
- * each kept for later calls.  Waits for completion and returns SCMD_ENONFINITE
+ * each kept for later calls; clusters small enough to live in one workgroup
+ * are stepped inside one kernel.  Waits for completion and returns SCMD_ENONFINITE
  * if an energy became non-finite during these steps (the state is then
  * undefined). */
 int scmd_step(scmd_ctx *ctx, int64_t nsteps);
@@ -398,7 +399,9 @@ int scmd_set_state(scmd_ctx *ctx, const void *buf, size_t bytes);
  * between graph kernels cost a few microseconds, so a graph is sampled once
  * per replay; the sample of its last replay in each scmd_step call is kept).
  * Changing the setting re-captures the graphs; enable = 0 stops recording;
- * every call resets the averages. */
+ * every call resets the averages.  Small clusters that otherwise run a whole
+ * call in one kernel take separate sweeps while the setting is on (results
+ * then differ in the last bits, by summation order). */
 int scmd_set_profiling(scmd_ctx *ctx, int enable);
 
 /* Average device milliseconds per launch of a kernel class over the launches

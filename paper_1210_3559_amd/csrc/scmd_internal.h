@@ -242,6 +242,19 @@ hipError_t launch_row_force(const RowLaunch &L, const SweepBuffers &B, const Ste
 hipError_t launch_bath_prep(const StepArgs &a, const int32_t *atom_cluster, const double4 *rp, const double4 *v,
                             const double4 *f, double2 *dpv, int natoms, hipStream_t s);
 
+// Resident runs (resident.hip): nsteps steps of every cluster, each in one
+// workgroup, in one launch (0: rho, F and energies at the current positions);
+// the cluster states are complete afterwards.  All pairs, every cluster at most
+// kResidentMax atoms.
+// kResidentMax is what one CU's LDS holds; a few clusters alone gain up to
+// kResidentFew atoms.  us per step, row sweeps / resident: 13 atoms 9.8 / 1.4,
+// 55: 10.2 / 3.6, 100 (bath): 11.1 / 6.6, 147: 10.3 / 9.1, 160: 10.3 / 10.7; 200
+// clusters of 150 22.6 / 9.5, 600 of 55 18.5 / 6.8, 20 of 147 11.9 / 10.3.
+constexpr int kResidentMax = 190;
+constexpr int kResidentFew = 152;
+hipError_t launch_resident(const SweepBuffers &B, const StepArgs &a, int nclusters, int nmax, int nsteps,
+                           const PotConst &pc, int precision, hipStream_t s);
+
 // Per-cluster energies, temperature and thermostat factor from the tile sums;
 // step_add = steps completed since the cluster step counter was last stored
 // (1 after every step; 0 for an evaluation without motion).

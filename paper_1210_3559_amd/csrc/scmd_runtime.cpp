@@ -53,6 +53,8 @@ hipError_t scratch_address(int device, void **out) {
 }
 
 constexpr int kGraphSteps = 32;  // steps per captured graph
+constexpr int kResidentEval = 96;
+constexpr int64_t kResidentSteps = 1024;  // steps per launch of a resident run (a few ms)
 
 struct EvPair {
     hipEvent_t a = nullptr, b = nullptr;
@@ -147,6 +149,7 @@ struct scmd_ctx {
     bool has_split = false;  // some tile's partner range spans several items
 
     // symmetric all-pairs plan
+    bool resident = false;  // whole runs of small clusters in one kernel (the row plan stands by for profiling)
     bool row = false;       // row sweeps (small clusters, no partial slots)
     int row_waves = 16;
     int row_uni_off = 0, row_uni_n = 0, row_uni_ni = 0;  // single-cluster row plan (ni = 0: tables)
@@ -527,6 +530,7 @@ int build_row_plan(scmd_ctx *c, int target, std::vector<ITile> *tiles_out) {
 int build_plan(scmd_ctx *c, std::vector<ITile> *tiles_out) {
     c->plan_ok = false;
     c->row = false;
+    c->resident = false;
     {
         int64_t nmax = 0;
         for (int k = 0; k < c->nclusters; ++k) nmax = std::max<int64_t>(nmax, c->offsets[k + 1] - c->offsets[k]);
@@ -547,14 +551,21 @@ int build_plan(scmd_ctx *c, std::vector<ITile> *tiles_out) {
         // symmetric: 3001 atoms 24.1 / 25.1, 3501 atoms 39 / 28; batches 4 x
         // 2057 36.7 / 30.7, 30 x 500 26.2 / 23.2, but 100 x 300 25.3 / 28.1
         // (a cluster of few 64-atom tiles wastes lanes and runs mostly in
-        // diagonal items).  Generic exponents have no symmetric form.
-        const bool row_single = nmax <= (c->pc.generic ? kRowStageMax : kRowSingleMax);
+        // diagonal items).  Generic exponents have no symmetric form, and in
+        // mixed precision the symmetric coefficient rounds P_i and P_j in one
+        // order for both atoms: those keep the row sweeps wherever the
+        // clusters can be staged.
+        const bool wide = c->pc.generic || c->precision == SCMD_MIXED;
+        const bool row_single = nmax <= (wide ? kRowStageMax : kRowSingleMax);
         const bool row_batch = nmax <= kRowStageMax &&
-                               upairs <= (c->pc.generic || nmax <= kRowBatchSmall ? kRowBatchPairs : kRowBatchPairsLarge);
+                               upairs <= (wide || nmax <= kRowBatchSmall ? kRowBatchPairs : kRowBatchPairsLarge);
         const bool row_default = !shape_given && (batch ? row_batch : row_single);
         if (c->neighbour == SCMD_ALLPAIRS && (c->tuning.pairs == 3 || (c->tuning.pairs == 0 && row_default))) {
             c->sym = false;
             c->row = true;
+            // (kResidentMax: both sides measured)
+            c->resident = c->tuning.pairs == 0 && c->natoms > 0 &&
+                          nmax <= (c->nclusters >= 16 ? kResidentMax : kResidentFew);
             c->row_waves = c->tuning.waves_j > 0 ? c->tuning.waves_j : 8;
             return build_row_plan(c, c->tuning.target_items > 0 ? c->tuning.target_items : 256, tiles_out);
         }
@@ -749,6 +760,10 @@ bool folds_drift(const scmd_ctx *c) {
     return c->natoms > 0 && ((c->row && c->row_nmax <= kRowStageMax) || (c->sym && c->sym_waves == 4));
 }
 
+// Whether whole runs go to the resident kernel; while the sweeps are being
+// profiled they run as launches of their own.
+bool runs_resident(const scmd_ctx *c) { return c->resident && !c->profiling; }
+
 // One pair sweep (with its profiling events).  energy = 0 lets the force
 // sweep skip the pair energy (steps whose energies nobody reads).  Row
 // sweeps of staged clusters take the drift (drift_mode, local: Drift)
@@ -826,6 +841,10 @@ hipError_t enqueue_sweeps(scmd_ctx *c, hipStream_t s, bool capturing, int advanc
 // rho, F, energies at the current positions; advance = 1 also kicks and
 // runs the thermostat (second half of a step).
 hipError_t enqueue_forces(scmd_ctx *c, hipStream_t s, bool capturing, int advance) {
+    // one evaluation of more than kResidentEval atoms is faster on the whole
+    // chip (147 atoms with its copies: 82.9 us on the row sweeps, 85.3 here)
+    if (runs_resident(c) && !advance && c->row_nmax <= kResidentEval)
+        return launch_resident(buffers(c), step_args(c, 0), c->nclusters, c->row_nmax, 0, c->pc, c->precision, s);
     hipError_t e = enqueue_sweeps(c, s, capturing, advance);
     if (e != hipSuccess) return e;
     return launch_finalize(step_args(c, advance), c->d_tile_sums.p, c->nclusters, advance, s);
@@ -946,6 +965,13 @@ int sync_and_check(scmd_ctx *c) {
 // every replay ends with the per-cluster finalize, so the state is complete
 // after it.  Eager launches only when profiling events cannot be captured.
 int enqueue_chunk(scmd_ctx *c, int64_t nsteps) {
+    if (runs_resident(c)) {  // nothing to capture: a launch is up to kResidentSteps steps
+        for (int64_t left = nsteps; left > 0; left -= kResidentSteps)
+            HIP_TRY(c, launch_resident(buffers(c), step_args(c, 1), c->nclusters, c->row_nmax,
+                                       (int)std::min<int64_t>(left, kResidentSteps), c->pc, c->precision, c->stream));
+        c->step += nsteps;
+        return SCMD_OK;
+    }
     const bool use_graph = !(c->profiling && !c->graph_events_ok);
     int64_t full = use_graph ? nsteps / kGraphSteps : 0;
     int64_t rem = nsteps - full * kGraphSteps;

@@ -205,6 +205,65 @@ __device__ __forceinline__ void force_pair(double dx, double dy, double dz, bool
 }
 
 // ---------------------------------------------------------------------------
+// The terms of one pair from its r^2 (no mask, no cutoff): what one atom's sum
+// and the other's share.
+// ---------------------------------------------------------------------------
+// u^m.
+template <int PREC, bool GEN>
+__device__ __forceinline__ double density_term(double r2, const PotConst &pc) {
+    if constexpr (PREC == SCMD_FP64) {
+        if constexpr (GEN) return (pc.m & 1) == 0 ? powi(rcp_nr(r2), pc.m >> 1) : powi(rsq_nr(r2), pc.m);
+        const double w = rcp_nr(r2);
+        return w * w * w;
+    } else {
+        const float x = (float)r2;
+        if constexpr (GEN)
+            return (double)((pc.m & 1) == 0 ? powi(__builtin_amdgcn_rcpf(x), pc.m >> 1)
+                                            : powi(__builtin_amdgcn_rsqf(x), pc.m));
+        const float w = __builtin_amdgcn_rcpf(x);
+        return (double)(w * w * w);
+    }
+}
+
+// The force coefficient (scaled as in force_pair) and, with EN, u^n.
+template <int PREC, bool GEN, bool EN>
+__device__ __forceinline__ void force_coef(double r2, double ci, double pj, float cif, float pjf, double &f,
+                                           double &un, const PotConst &pc, float Af) {
+    if constexpr (PREC == SCMD_FP64) {
+        if constexpr (!GEN) {
+            const double w = rsq2_nr(r2);  // 2u
+            const double w2 = w * w;
+            const double w3 = w2 * w;
+            const double w4 = w2 * w2;
+            const double w8 = w4 * w4;
+            const double q = __builtin_fma(pc.A8, w3, ci) - pj;
+            f = w8 * q;
+            if constexpr (EN) un = w8 * w;
+        } else {
+            const double u = rsq_nr(r2);
+            const double q = __builtin_fma(pc.A, powi(u, pc.n - pc.m), ci) - pj;
+            f = powi(u, pc.m + 2) * q;
+            if constexpr (EN) un = powi(u, pc.n);
+        }
+    } else {
+        const float u = __builtin_amdgcn_rsqf((float)r2);
+        if constexpr (!GEN) {
+            const float u2 = u * u;
+            const float u3 = u2 * u;
+            const float u4 = u2 * u2;
+            const float u8 = u4 * u4;
+            const float q = __builtin_fmaf(Af, u3, cif) - pjf;
+            f = (double)(u8 * q);
+            if constexpr (EN) un = (double)(u8 * u);
+        } else {
+            const float q = __builtin_fmaf(Af, powi(u, pc.n - pc.m), cif) - pjf;
+            f = (double)(powi(u, pc.m + 2) * q);
+            if constexpr (EN) un = (double)powi(u, pc.n);
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------
 // Workgroup helpers
 // ---------------------------------------------------------------------------
 // Fixed-shape tree sum over a workgroup of BLOCK threads (deterministic).

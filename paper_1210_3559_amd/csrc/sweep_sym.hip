@@ -81,28 +81,7 @@ __device__ __forceinline__ void sym_force_pair(double dx, double dy, double dz, 
                                                float pjf, double &fx, double &fy, double &fz, double &eu,
                                                double &gx, double &gy, double &gz, const PotConst &pc, float Af) {
     double f, un;
-    if constexpr (PREC == SCMD_FP64) {
-        // w = 2u; sums scaled by 2^8 (force) and 2^9 (u^n), see force_pair
-        const double r2 = __builtin_fma(dx, dx, __builtin_fma(dy, dy, dz * dz));
-        const double w = rsq2_nr(r2);
-        const double w2 = w * w;
-        const double w3 = w2 * w;
-        const double w4 = w2 * w2;
-        const double w8 = w4 * w4;
-        const double q = __builtin_fma(pc.A8, w3, ci) - pj;
-        f = w8 * q;
-        if constexpr (EN) un = w8 * w;
-    } else {
-        const double r2d = __builtin_fma(dx, dx, __builtin_fma(dy, dy, dz * dz));
-        const float u = __builtin_amdgcn_rsqf((float)r2d);
-        const float u2 = u * u;
-        const float u3 = u2 * u;
-        const float u4 = u2 * u2;
-        const float u8 = u4 * u4;
-        const float q = __builtin_fmaf(Af, u3, cif) - pjf;
-        f = (double)(u8 * q);
-        if constexpr (EN) un = (double)(u8 * u);
-    }
+    force_coef<PREC, false, EN>(__builtin_fma(dx, dx, __builtin_fma(dy, dy, dz * dz)), ci, pj, cif, pjf, f, un, pc, Af);
     fx = __builtin_fma(f, dx, fx);
     fy = __builtin_fma(f, dy, fy);
     fz = __builtin_fma(f, dz, fz);
@@ -325,18 +304,6 @@ __global__ __launch_bounds__(64 * NW) void k_sym_force(const SymItem *__restrict
 // ---------------------------------------------------------------------------
 // Density sweep
 // ---------------------------------------------------------------------------
-// (a/r)^m / a^m = u^6 of one pair ((n, m) = (9, 6)).
-template <int PREC>
-__device__ __forceinline__ double sym_density_term(double dx, double dy, double dz) {
-    if constexpr (PREC == SCMD_FP64) {
-        const double w = rcp_nr(__builtin_fma(dx, dx, __builtin_fma(dy, dy, dz * dz)));
-        return w * w * w;
-    } else {
-        const float w = __builtin_amdgcn_rcpf((float)__builtin_fma(dx, dx, __builtin_fma(dy, dy, dz * dz)));
-        return (double)(w * w * w);
-    }
-}
-
 // With four wavefronts the sweep can also drift the atoms it loads
 // (da.mode != 0, see Drift): every item finishes its cluster's thermostat
 // factor for itself, and the cluster's first item stores it.
@@ -345,7 +312,7 @@ __global__ __launch_bounds__(64 * NW) void k_sym_density(const SymItem *__restri
                                                          const int32_t *__restrict__ order,
                                                          const SymTile *__restrict__ tiles,
                                                          const double4 *__restrict__ rp, double *__restrict__ ipart,
-                                                         double *__restrict__ jpart, DriftArgs da) {
+                                                         double *__restrict__ jpart, PotConst pc, DriftArgs da) {
     constexpr int RW = 64 / NW;
     constexpr int SI = NW * IPT * 64;
     __shared__ double sh[NW == 1 ? 1 : 2 * SI];
@@ -367,6 +334,9 @@ __global__ __launch_bounds__(64 * NW) void k_sym_density(const SymItem *__restri
             if (da.mode != 0) return drifted_atom(rp, i, da, bath, lam);
         }
         return rp[i];
+    };
+    auto pair_term = [&](double dx, double dy, double dz) {
+        return density_term<PREC, false>(__builtin_fma(dx, dx, __builtin_fma(dy, dy, dz * dz)), pc);
     };
     IGroup<IPT> G;
     load_group<IPT>(it, tiles, position, G);
@@ -391,11 +361,11 @@ __global__ __launch_bounds__(64 * NW) void k_sym_density(const SymItem *__restri
 #pragma unroll
                     for (int p = 0; p < IPT; ++p) {
                         if (p < b) {
-                            const double t6 = sym_density_term<PREC>(G.x[p] - xj, G.y[p] - yj, G.z[p] - zj);
+                            const double t6 = pair_term(G.x[p] - xj, G.y[p] - yj, G.z[p] - zj);
                             acc[p] += t6;
                             rj += t6;
                         } else if (p == b && with_own_tile) {
-                            acc[p] += sym_density_term<PREC>(G.x[p] - xj, G.y[p] - yj, G.z[p] - zj);
+                            acc[p] += pair_term(G.x[p] - xj, G.y[p] - yj, G.z[p] - zj);
                         }
                     }
                     xj = ror1(xj);
@@ -447,7 +417,7 @@ __global__ __launch_bounds__(64 * NW) void k_sym_density(const SymItem *__restri
                 }
 #pragma unroll
                 for (int p = 0; p < IPT; ++p) {
-                    const double t6 = sym_density_term<PREC>(G.x[p] - xj, G.y[p] - yj, G.z[p] - zj);
+                    const double t6 = pair_term(G.x[p] - xj, G.y[p] - yj, G.z[p] - zj);
                     acc[p] += t6;
                     rj += t6;
                 }
@@ -599,7 +569,7 @@ hipError_t launch_ipt(bool force, int stage, bool energy, const SymLaunch &L, co
                                L.tiles, B.xp, L.ipart, L.jpart, pc);
         else
             hipLaunchKernelGGL((k_sym_density<IPT, PREC, NW>), dim3(L.nitems), block, 0, s, L.items, L.order, L.tiles,
-                               B.rp, L.ipart, L.jpart, da);
+                               B.rp, L.ipart, L.jpart, pc, da);
     }
     if (stage == 1 && L.ntiles > 0) {
         if (force) {
