@@ -467,6 +467,10 @@ int build_row_plan(scmd_ctx *c, int target, std::vector<ITile> *tiles_out) {
         const int off = (int)c->offsets[k];
         const int n = (int)(c->offsets[k + 1] - c->offsets[k]);
         int ni = n > 0 ? (int)std::min<double>(ni_cap, std::max(1.0, std::ceil(wstar / n))) : 1;
+        // a cluster of its own: at least two atoms per workgroup, whose group
+        // sums one thread each adds in a row (160 atoms 10.3 us per step with
+        // one, 9.1 with two)
+        if (c->nclusters == 1) ni = std::max(ni, std::min(2, n));
         // each atom of a tile gets floor(groups / ni) of the 8-lane groups;
         // when that leaves more than a tenth of the groups idle, take the
         // largest power of two <= ni instead (it divides the group count)
@@ -566,7 +570,12 @@ int build_plan(scmd_ctx *c, std::vector<ITile> *tiles_out) {
             // (kResidentMax: both sides measured)
             c->resident = c->tuning.pairs == 0 && c->natoms > 0 &&
                           nmax <= (c->nclusters >= 16 ? kResidentMax : kResidentFew);
-            c->row_waves = c->tuning.waves_j > 0 ? c->tuning.waves_j : 8;
+            // one workgroup per CU from about 2560 atoms on (two no longer fit
+            // the LDS), so the runs have to divide the groups evenly: 16
+            // wavefronts do where 8 leave a fifth of them idle or need a
+            // second round (2600 atoms 32.3 us per step at 8, 21.1 at 16; 2243
+            // 17.7 / 18.2)
+            c->row_waves = c->tuning.waves_j > 0 ? c->tuning.waves_j : batch || nmax <= 2560 ? 8 : 16;
             return build_row_plan(c, c->tuning.target_items > 0 ? c->tuning.target_items : 256, tiles_out);
         }
         c->sym = allowed && (c->tuning.pairs == 2 || (c->tuning.pairs == 0 && (batch || nmax > 4096)));

@@ -40,6 +40,13 @@ template <int IPT, int PREC, bool GEN, bool MASK>
 __device__ __forceinline__ void density_range(const double4 *__restrict__ rp, int ja, int jb, const double *xi,
                                               const double *yi, const double *zi, const int *gi, double *acc,
                                               const PotConst &pc) {
+    if constexpr (GEN && !MASK && IPT == 1) {
+        const double4 qi = make_double4(xi[0], yi[0], zi[0], 0.0);
+        for (; ja + 4 <= jb; ja += 4) {
+            const double4 a[4] = {rp[ja], rp[ja + 1], rp[ja + 2], rp[ja + 3]};
+            density_quad<PREC, GEN>(qi, a, acc[0], pc);
+        }
+    }
 #pragma unroll 4
     for (int j = ja; j < jb; ++j) {
         const double4 q = rp[j];
@@ -56,6 +63,13 @@ __device__ __forceinline__ void force_range(const double4 *__restrict__ xp, int 
                                             const double *yi, const double *zi, const double *ci, const float *cif,
                                             const int *gi, double *fx, double *fy, double *fz, double *eu,
                                             const PotConst &pc, float Af) {
+    if constexpr (GEN && !MASK && IPT == 1) {
+        const double4 qi = make_double4(xi[0], yi[0], zi[0], 0.0);
+        for (; ja + 4 <= jb; ja += 4) {
+            const double4 a[4] = {xp[ja], xp[ja + 1], xp[ja + 2], xp[ja + 3]};
+            force_quad<PREC, GEN, true>(qi, a, ci[0], cif[0], fx[0], fy[0], fz[0], eu[0], pc, Af);
+        }
+    }
 #pragma unroll 2
     for (int j = ja; j < jb; ++j) {
         const double4 q = xp[j];

@@ -4,6 +4,8 @@
 // (or every tile of a cluster) has arrived.
 #pragma once
 
+#include <type_traits>
+
 #include "../../include/scmd.h"
 #include "bath.h"
 #include "scmd_internal.h"
@@ -31,16 +33,82 @@ __device__ __forceinline__ double rsq_nr(double x) {
     return y * e;
 }
 
-template <typename T>
-__device__ __forceinline__ T powi(T x, int k) {
-    T r = T(1);
-    T b = x;
-    while (k > 0) {
-        if (k & 1) r *= b;
-        b *= b;
-        k >>= 1;
+// r[k][i] = b[i]^e[k] for E exponents at once (they share the squarings of b,
+// which is overwritten): wave-uniform exponents, so every test is a scalar
+// branch, taken once for all N values.
+template <typename T, int N, int E>
+__device__ __forceinline__ void powers(T (&b)[N], int (&e)[E], T (&r)[E][N]) {
+    int all = 0;
+#pragma unroll
+    for (int k = 0; k < E; ++k) {
+        all |= e[k];
+#pragma unroll
+        for (int i = 0; i < N; ++i) r[k][i] = T(1);
     }
-    return r;
+    for (;;) {
+#pragma unroll
+        for (int k = 0; k < E; ++k) {
+            if (e[k] & 1) {
+#pragma unroll
+                for (int i = 0; i < N; ++i) r[k][i] *= b[i];
+            }
+            e[k] >>= 1;
+        }
+        all >>= 1;
+        if (all == 0) break;
+#pragma unroll
+        for (int i = 0; i < N; ++i) b[i] *= b[i];
+    }
+}
+
+// General exponents, N pairs at a time: u^m from r^2 (in double also for the
+// mixed form, which then works in single precision).
+template <int PREC, int N>
+__device__ __forceinline__ void generic_density(const double (&r2)[N], const PotConst &pc, double (&t)[N]) {
+    using T = std::conditional_t<PREC == SCMD_FP64, double, float>;
+    T b[N], r[1][N];
+    const bool even = (pc.m & 1) == 0;  // even m: powers of 1/r^2
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        if constexpr (PREC == SCMD_FP64)
+            b[i] = even ? rcp_nr(r2[i]) : rsq_nr(r2[i]);
+        else
+            b[i] = even ? __builtin_amdgcn_rcpf((float)r2[i]) : __builtin_amdgcn_rsqf((float)r2[i]);
+    }
+    int e[1] = {even ? pc.m >> 1 : pc.m};
+    powers<T, N, 1>(b, e, r);
+#pragma unroll
+    for (int i = 0; i < N; ++i) t[i] = (double)r[0][i];
+}
+
+// The force coefficients u^(m+2) [A u^(n-m) - P_i - P_j] and, with EN, u^n.
+template <int PREC, int N, bool EN>
+__device__ __forceinline__ void generic_force(const double (&r2)[N], double ci, const double (&pj)[N], float cif,
+                                              const float (&pjf)[N], const PotConst &pc, float Af, double (&f)[N],
+                                              double (&un)[N]) {
+    using T = std::conditional_t<PREC == SCMD_FP64, double, float>;
+    constexpr int E = EN ? 3 : 2;
+    T b[N], r[E][N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        if constexpr (PREC == SCMD_FP64)
+            b[i] = rsq_nr(r2[i]);
+        else
+            b[i] = __builtin_amdgcn_rsqf((float)r2[i]);
+    }
+    int e[E];
+    e[0] = pc.m + 2;
+    e[1] = pc.n - pc.m;
+    if constexpr (EN) e[2] = pc.n;
+    powers<T, N, E>(b, e, r);
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        if constexpr (PREC == SCMD_FP64)
+            f[i] = r[0][i] * (__builtin_fma(pc.A, r[1][i], ci) - pj[i]);
+        else
+            f[i] = (double)(r[0][i] * (__builtin_fmaf(Af, r[1][i], cif) - pjf[i]));
+        if constexpr (EN) un[i] = (double)r[2][i];
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -61,7 +129,9 @@ __device__ __forceinline__ void density_pair(double dx, double dy, double dz, bo
             double w = rcp_nr(r2);  // u^2
             t = w * w * w;
         } else {
-            t = (pc.m & 1) == 0 ? powi(rcp_nr(r2), pc.m >> 1) : powi(rsq_nr(r2), pc.m);
+            double x[1] = {r2}, y[1];
+            generic_density<PREC, 1>(x, pc, y);
+            t = y[0];
         }
         if constexpr (CUT) {
             acc += off ? 0.0 : t - pc.inv_rc_m;
@@ -77,17 +147,19 @@ __device__ __forceinline__ void density_pair(double dx, double dy, double dz, bo
         if constexpr (MASK) off = off || self;
         float r2 = (float)r2d;
         if constexpr (MASK || CUT) r2 = off ? kSelfR2f : r2;
-        float t;
+        double t;
         if constexpr (!GEN) {
             float w = __builtin_amdgcn_rcpf(r2);
-            t = w * w * w;
+            t = (double)(w * w * w);
         } else {
-            t = (pc.m & 1) == 0 ? powi(__builtin_amdgcn_rcpf(r2), pc.m >> 1) : powi(__builtin_amdgcn_rsqf(r2), pc.m);
+            double x[1] = {(double)r2}, y[1];
+            generic_density<PREC, 1>(x, pc, y);
+            t = y[0];
         }
         if constexpr (CUT) {
-            acc += off ? 0.0 : (double)t - pc.inv_rc_m;
+            acc += off ? 0.0 : t - pc.inv_rc_m;
         } else {
-            acc += (double)t;
+            acc += t;
         }
     }
 }
@@ -151,12 +223,11 @@ __device__ __forceinline__ void force_pair(double dx, double dy, double dz, bool
             f = w8 * q;   // 2^8 x the force coefficient
             if constexpr (EN) un = w8 * w;  // 2^9 u^n
         } else {
-            double u = rsq_nr(r2);
-            double um2 = powi(u, pc.m + 2);
-            double und = powi(u, pc.n - pc.m);
-            double q = __builtin_fma(pc.A, und, ci) - pj;
-            f = um2 * q;
-            un = powi(u, pc.n);
+            double x[1] = {r2}, p[1] = {pj}, g[1], e[1];
+            float pf[1] = {pjf};
+            generic_force<PREC, 1, EN>(x, ci, p, cif, pf, pc, Af, g, e);
+            f = g[0];
+            if constexpr (EN) un = e[0];
         }
         fx = __builtin_fma(f, dx, fx);
         fy = __builtin_fma(f, dy, fy);
@@ -174,32 +245,31 @@ __device__ __forceinline__ void force_pair(double dx, double dy, double dz, bool
         if constexpr (MASK) off = off || self;
         float r2 = (float)r2d;
         if constexpr (MASK || CUT) r2 = off ? kSelfR2f : r2;
-        float u = __builtin_amdgcn_rsqf(r2);
-        float f, un;
+        double fd, un;
         if constexpr (!GEN) {
+            float u = __builtin_amdgcn_rsqf(r2);
             float u2 = u * u;
             float u3 = u2 * u;
             float u4 = u2 * u2;
             float u8 = u4 * u4;
             float q = __builtin_fmaf(Af, u3, cif) - pjf;
-            f = u8 * q;
-            if constexpr (EN) un = u8 * u;
+            fd = (double)(u8 * q);
+            if constexpr (EN) un = (double)(u8 * u);
         } else {
-            float um2 = powi(u, pc.m + 2);
-            float und = powi(u, pc.n - pc.m);
-            float q = __builtin_fmaf(Af, und, cif) - pjf;
-            f = um2 * q;
-            un = powi(u, pc.n);
+            double x[1] = {(double)r2}, p[1] = {pj}, g[1], e[1];
+            float pf[1] = {pjf};
+            generic_force<PREC, 1, EN>(x, ci, p, cif, pf, pc, Af, g, e);
+            fd = g[0];
+            if constexpr (EN) un = e[0];
         }
-        double fd = (double)f;
         fx = __builtin_fma(fd, dx, fx);
         fy = __builtin_fma(fd, dy, fy);
         fz = __builtin_fma(fd, dz, fz);
         if constexpr (!EN) {
         } else if constexpr (CUT) {
-            eu += off ? 0.0 : (double)un - pc.inv_rc_n;
+            eu += off ? 0.0 : un - pc.inv_rc_n;
         } else {
-            eu += (double)un;
+            eu += un;
         }
     }
 }
@@ -211,16 +281,15 @@ __device__ __forceinline__ void force_pair(double dx, double dy, double dz, bool
 // u^m.
 template <int PREC, bool GEN>
 __device__ __forceinline__ double density_term(double r2, const PotConst &pc) {
-    if constexpr (PREC == SCMD_FP64) {
-        if constexpr (GEN) return (pc.m & 1) == 0 ? powi(rcp_nr(r2), pc.m >> 1) : powi(rsq_nr(r2), pc.m);
+    if constexpr (GEN) {
+        double x[1] = {r2}, t[1];
+        generic_density<PREC, 1>(x, pc, t);
+        return t[0];
+    } else if constexpr (PREC == SCMD_FP64) {
         const double w = rcp_nr(r2);
         return w * w * w;
     } else {
-        const float x = (float)r2;
-        if constexpr (GEN)
-            return (double)((pc.m & 1) == 0 ? powi(__builtin_amdgcn_rcpf(x), pc.m >> 1)
-                                            : powi(__builtin_amdgcn_rsqf(x), pc.m));
-        const float w = __builtin_amdgcn_rcpf(x);
+        const float w = __builtin_amdgcn_rcpf((float)r2);
         return (double)(w * w * w);
     }
 }
@@ -229,36 +298,84 @@ __device__ __forceinline__ double density_term(double r2, const PotConst &pc) {
 template <int PREC, bool GEN, bool EN>
 __device__ __forceinline__ void force_coef(double r2, double ci, double pj, float cif, float pjf, double &f,
                                            double &un, const PotConst &pc, float Af) {
-    if constexpr (PREC == SCMD_FP64) {
-        if constexpr (!GEN) {
-            const double w = rsq2_nr(r2);  // 2u
-            const double w2 = w * w;
-            const double w3 = w2 * w;
-            const double w4 = w2 * w2;
-            const double w8 = w4 * w4;
-            const double q = __builtin_fma(pc.A8, w3, ci) - pj;
-            f = w8 * q;
-            if constexpr (EN) un = w8 * w;
-        } else {
-            const double u = rsq_nr(r2);
-            const double q = __builtin_fma(pc.A, powi(u, pc.n - pc.m), ci) - pj;
-            f = powi(u, pc.m + 2) * q;
-            if constexpr (EN) un = powi(u, pc.n);
-        }
+    if constexpr (GEN) {
+        double x[1] = {r2}, p[1] = {pj}, g[1], e[1];
+        float pf[1] = {pjf};
+        generic_force<PREC, 1, EN>(x, ci, p, cif, pf, pc, Af, g, e);
+        f = g[0];
+        if constexpr (EN) un = e[0];
+    } else if constexpr (PREC == SCMD_FP64) {
+        const double w = rsq2_nr(r2);  // 2u
+        const double w2 = w * w;
+        const double w3 = w2 * w;
+        const double w4 = w2 * w2;
+        const double w8 = w4 * w4;
+        const double q = __builtin_fma(pc.A8, w3, ci) - pj;
+        f = w8 * q;
+        if constexpr (EN) un = w8 * w;
     } else {
         const float u = __builtin_amdgcn_rsqf((float)r2);
-        if constexpr (!GEN) {
-            const float u2 = u * u;
-            const float u3 = u2 * u;
-            const float u4 = u2 * u2;
-            const float u8 = u4 * u4;
-            const float q = __builtin_fmaf(Af, u3, cif) - pjf;
-            f = (double)(u8 * q);
-            if constexpr (EN) un = (double)(u8 * u);
-        } else {
-            const float q = __builtin_fmaf(Af, powi(u, pc.n - pc.m), cif) - pjf;
-            f = (double)(powi(u, pc.m + 2) * q);
-            if constexpr (EN) un = (double)powi(u, pc.n);
+        const float u2 = u * u;
+        const float u3 = u2 * u;
+        const float u4 = u2 * u2;
+        const float u8 = u4 * u4;
+        const float q = __builtin_fmaf(Af, u3, cif) - pjf;
+        f = (double)(u8 * q);
+        if constexpr (EN) un = (double)(u8 * u);
+    }
+}
+
+// Four partners of one atom, in order (no mask, no cutoff).  General exponents
+// take them together, which shares the exponent tests among four pairs and
+// gives the power chains four independent values: a 3001-atom evaluation with
+// (12, 6) took 20.4 + 44.0 us (density, force sweep) pair by pair.
+template <int PREC, bool GEN>
+__device__ __forceinline__ void density_quad(const double4 &qi, const double4 (&a)[4], double &acc,
+                                             const PotConst &pc) {
+    if constexpr (!GEN) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            density_pair<PREC, GEN, false, false>(qi.x - a[i].x, qi.y - a[i].y, qi.z - a[i].z, false, acc, pc);
+    } else {
+        double r2[4], t[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const double dx = qi.x - a[i].x, dy = qi.y - a[i].y, dz = qi.z - a[i].z;
+            r2[i] = __builtin_fma(dx, dx, __builtin_fma(dy, dy, dz * dz));
+        }
+        generic_density<PREC, 4>(r2, pc, t);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc += t[i];
+    }
+}
+
+template <int PREC, bool GEN, bool EN>
+__device__ __forceinline__ void force_quad(const double4 &qi, const double4 (&a)[4], double ci, float cif, double &fx,
+                                           double &fy, double &fz, double &eu, const PotConst &pc, float Af) {
+    if constexpr (!GEN) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            force_pair<PREC, GEN, false, false, EN>(qi.x - a[i].x, qi.y - a[i].y, qi.z - a[i].z, false, ci, a[i].w, cif,
+                                                    (float)a[i].w, fx, fy, fz, eu, pc, Af);
+    } else {
+        double dx[4], dy[4], dz[4], r2[4], pj[4], f[4], un[4];
+        float pjf[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            dx[i] = qi.x - a[i].x;
+            dy[i] = qi.y - a[i].y;
+            dz[i] = qi.z - a[i].z;
+            r2[i] = __builtin_fma(dx[i], dx[i], __builtin_fma(dy[i], dy[i], dz[i] * dz[i]));
+            pj[i] = a[i].w;
+            pjf[i] = (float)a[i].w;
+        }
+        generic_force<PREC, 4, EN>(r2, ci, pj, cif, pjf, pc, Af, f, un);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            fx = __builtin_fma(f[i], dx[i], fx);
+            fy = __builtin_fma(f[i], dy[i], fy);
+            fz = __builtin_fma(f[i], dz[i], fz);
+            if constexpr (EN) eu += un[i];
         }
     }
 }

@@ -181,10 +181,10 @@ constexpr size_t row_lds_bytes(int n) {
 // The partner loop over rounds k in [ka, kb) of this thread's stream: plain
 // rounds in blocks of four through pointers stepped by 4 S, masked rounds
 // (self window, end of the cluster) one by one.  src points at the cluster's
-// first atom (LDS or global); pair(q, self) adds one partner.
-template <typename PAIR>
+// first atom (LDS or global); pair(q, self) adds one partner, quad(a) four.
+template <typename PAIR, typename QUAD>
 __device__ __forceinline__ void row_loop(const RowLayout &L, const double4 *__restrict__ src, int n, int i_local,
-                                         PAIR &&pair, int ka, int kb) {
+                                         PAIR &&pair, QUAD &&quad, int ka, int kb) {
     const int S = L.S;
     int k = ka;
     auto plain = [&](int k1) {
@@ -194,11 +194,8 @@ __device__ __forceinline__ void row_loop(const RowLayout &L, const double4 *__re
             const double4 *p1 = p0 + S, *p2 = p1 + S, *p3 = p2 + S;
             const size_t S4 = 4 * (size_t)S;
             for (; k + 4 <= k1; k += 4, p0 += S4, p1 += S4, p2 += S4, p3 += S4) {
-                const double4 a = *p0, b = *p1, c = *p2, e = *p3;
-                pair(a, false);
-                pair(b, false);
-                pair(c, false);
-                pair(e, false);
+                const double4 a[4] = {*p0, *p1, *p2, *p3};
+                quad(a);
             }
         }
         for (; k < k1; ++k, p0 += S) pair(*p0, false);
@@ -267,6 +264,7 @@ __global__ __launch_bounds__(64 * W) void k_row_density(RowArgs ra, DensityOut o
         else
             density_pair<PREC, GEN, false, false>(qi.x - a.x, qi.y - a.y, qi.z - a.z, false, acc, pc);
     };
+    auto quad = [&](const double4 (&a)[4]) { density_quad<PREC, GEN>(qi, a, acc, pc); };
     const double4 *src = o.rp + rt.off;
     double *sh = reinterpret_cast<double *>(lds_row);
     if constexpr (STAGE) {
@@ -317,11 +315,11 @@ __global__ __launch_bounds__(64 * W) void k_row_density(RowArgs ra, DensityOut o
             }
             __syncthreads();
         }
-        row_loop(L, lj, rt.n, i_local, pair, 0, L.k_end);
+        row_loop(L, lj, rt.n, i_local, pair, quad, 0, L.k_end);
         src = lj;
     } else {
         qi = src[i_local];
-        row_loop(L, src, rt.n, i_local, pair, 0, L.k_end);
+        row_loop(L, src, rt.n, i_local, pair, quad, 0, L.k_end);
     }
     double v[1] = {acc};
     row_reduce<W, 1>(L, v, sh);
@@ -361,6 +359,7 @@ __global__ __launch_bounds__(64 * W) void k_row_force(RowArgs ra, const double4 
             force_pair<PREC, GEN, false, false, EN>(qi.x - a.x, qi.y - a.y, qi.z - a.z, false, ci, a.w, cif,
                                                     (float)a.w, fx, fy, fz, eu, pc, Af);
     };
+    auto quad = [&](const double4 (&a)[4]) { force_quad<PREC, GEN, EN>(qi, a, ci, cif, fx, fy, fz, eu, pc, Af); };
     // the epilogue's own-atom loads are issued now, off the critical path
     double4 v_own = make_double4(0, 0, 0, 0), f_own = make_double4(0, 0, 0, 0);
     const bool bath = BATH && o.fused && (o.bath == 1 || (o.bath == 2 && o.cd[rt.c].kind == SCMD_LANGEVIN));
@@ -391,11 +390,11 @@ __global__ __launch_bounds__(64 * W) void k_row_force(RowArgs ra, const double4 
         double4 *lj = lds_row;
         sh += 4 * (size_t)rt.n;
         stage_copy<W>(lj, src, rt.n, draw);
-        row_loop(L, lj, rt.n, i_local, pair, 0, L.k_end);
+        row_loop(L, lj, rt.n, i_local, pair, quad, 0, L.k_end);
         src = lj;
     } else {
         draw();
-        row_loop(L, src, rt.n, i_local, pair, 0, L.k_end);
+        row_loop(L, src, rt.n, i_local, pair, quad, 0, L.k_end);
     }
     unscale_force<PREC, GEN>(fx, fy, fz, eu);
     if constexpr (!EN) eu = 0.0;
@@ -438,12 +437,12 @@ hipError_t row_launch(bool force, bool energy, const RowLaunch &L, const SweepBu
     hipError_t e;
     if (force) {
         const size_t lds = row_lds_bytes<W, 4, STAGE>(L.nmax);
-        // the generic-exponent kernels always accumulate the energy
         // the bath epilogue exists only in fused (staged) launches
         constexpr bool kB = STAGE;
-        auto kern = (energy || GEN)
-                        ? (fo.bath ? k_row_force<W, PREC, GEN, STAGE, true, kB> : k_row_force<W, PREC, GEN, STAGE, true, false>)
-                        : (fo.bath ? k_row_force<W, PREC, GEN, STAGE, GEN, kB> : k_row_force<W, PREC, GEN, STAGE, GEN, false>);
+        auto kern = energy ? (fo.bath ? k_row_force<W, PREC, GEN, STAGE, true, kB>
+                                      : k_row_force<W, PREC, GEN, STAGE, true, false>)
+                           : (fo.bath ? k_row_force<W, PREC, GEN, STAGE, false, kB>
+                                      : k_row_force<W, PREC, GEN, STAGE, false, false>);
         if ((e = allow_lds(kern, lds)) != hipSuccess) return e;
         hipLaunchKernelGGL(kern, dim3(L.ntiles), dim3(64 * W), lds, s, ra, (const double4 *)B.xp, fo, pc);
     } else {
