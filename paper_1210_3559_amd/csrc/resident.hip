@@ -291,7 +291,7 @@ __global__ __launch_bounds__(kResBlock, 4) void k_resident(ResidentArgs o, PotCo
         q.temp = q.lambda * q.lambda * kt.T;
         if (!isfinite(q.epot) || !isfinite(q.ekin)) {
             q.nonfinite = 1;
-            atomicOr(o.flag, 1);
+            raise_flag(o.flag);
         }
         o.st[c] = q;
     }

@@ -135,7 +135,7 @@ struct CellCheck {
 struct StepArgs {
     const ClusterDesc *cd;
     ClusterState *st;
-    int *flag;          // non-finite flag
+    int *flag;          // non-finite flag (pinned host memory)
     double mass_u, dt, h;
     int advance;        // 1: kick + thermostat (second half of a step); 0: evaluate only
     int energy;         // 1: accumulate the pair energy (symmetric and row force sweeps skip it otherwise)
@@ -272,7 +272,14 @@ hipError_t launch_drift_fin(const StepArgs &a, const double *tile_sums, int loca
 hipError_t launch_drift(const int32_t *atom_cluster, const ClusterDesc *cd, const ClusterState *st, double4 *rp,
                         double4 *v, const double4 *f, int natoms, double mass_u, double dt, double h, int local,
                         hipStream_t s);
-hipError_t launch_aos_from4(const double4 *src, double *dst, int natoms, hipStream_t s);
+// x, y, z of the atoms [first, first + count), packed (st: times the pending
+// thermostat factor of the atom's cluster).
+hipError_t launch_xyz(const double4 *src, const ClusterState *st, const int32_t *atom_cluster, int first, int count,
+                      double *dst, hipStream_t s);
+hipError_t launch_copy_words(const uint64_t *src, uint64_t *dst, size_t n, hipStream_t s);
+// Samples number [first, first + count) of one cluster (5 doubles each).
+hipError_t launch_fetch_samples(const double *ring, int cap, int nclusters, int cluster, int64_t first, int count,
+                                double *dst, hipStream_t s);
 // Append the state of every cluster to ring slot `slot` (5 doubles per
 // cluster: step, E_pot, E_kin, T, T_target).
 hipError_t launch_sample(const ClusterState *st, int nclusters, double *ring, int slot, int64_t step, hipStream_t s);

@@ -119,10 +119,8 @@ struct scmd_ctx {
     DevBuf<int32_t> atom_cluster;
     DevBuf<ClusterDesc> d_cdesc;
     DevBuf<ClusterState> d_state;
-    DevBuf<int> d_flag;
     DevBuf<int32_t> rdf_refs;
-    DevBuf<int> rdf_nref;
-    DevBuf<unsigned long long> rdf_counts;
+    DevBuf<unsigned long long> rdf_counts;  // the histogram, then the number of reference atoms
     // frame stores of the diffusion coefficient (one per cluster that has one)
     struct FrameStore {
         int cluster = 0;
@@ -132,9 +130,22 @@ struct scmd_ctx {
     };
     std::vector<FrameStore> frames;
     void *scratch = nullptr;  // this device's fixed scratch array (scmd_rdf_noalloc)
-    DevBuf<double> diff_seg;  // per-segment coefficients, then the mean
-    DevBuf<int> diff_ncentral;
-    int *h_flag = nullptr;  // pinned
+    DevBuf<double> diff_seg;  // per-segment coefficients
+    // Pinned host memory, written by kernels: the non-finite flag (kept apart
+    // from h_flag, the host's view of it at the last synchronisation), results
+    // of a few words, and the staging area of the getters.  A getter is one
+    // small kernel and one synchronisation; a device-to-host copy into
+    // pageable memory costs two to four times that (Ni147: 83 us for an
+    // evaluation with energies, forces and densities).
+    struct Pinned {
+        int flag;
+        int n_central;
+        double diffusion;
+        alignas(64) unsigned char stage[1 << 18];
+    };
+    Pinned *pin = nullptr;
+    hipEvent_t stage_ev[2] = {nullptr, nullptr};
+    int h_flag = 0;
 
     // all-pairs plan
     bool plan_ok = false;
@@ -742,7 +753,7 @@ hipError_t record(hipEvent_t ev, hipStream_t s, bool capturing) {
 double half_kick(const scmd_ctx *c) { return 0.5 * c->dt / (c->mass * kEvPerUA2Fs2); }
 
 StepArgs step_args(scmd_ctx *c, int advance, int energy = 1) {
-    return StepArgs{c->d_cdesc.p, c->d_state.p, c->d_flag.p, c->mass, c->dt, half_kick(c), advance, energy};
+    return StepArgs{c->d_cdesc.p, c->d_state.p, &c->pin->flag, c->mass, c->dt, half_kick(c), advance, energy};
 }
 
 SweepBuffers buffers(scmd_ctx *c) {
@@ -962,10 +973,33 @@ int check_ready(scmd_ctx *c) {
 }
 
 int sync_and_check(scmd_ctx *c) {
-    HIP_TRY(c, hipMemcpyAsync(c->h_flag, c->d_flag.p, sizeof(int), hipMemcpyDeviceToHost, c->stream));
     HIP_TRY(c, hipStreamSynchronize(c->stream));
+    c->h_flag = __atomic_load_n(&c->pin->flag, __ATOMIC_RELAXED);
     if (c->profiling) harvest_events(c);
-    if (*c->h_flag) return fail(c, SCMD_ENONFINITE, "a cluster energy became non-finite (coincident or overlapping atoms?)");
+    if (c->h_flag) return fail(c, SCMD_ENONFINITE, "a cluster energy became non-finite (coincident or overlapping atoms?)");
+    return SCMD_OK;
+}
+
+// Device words to the caller's memory through the staging area's two halves:
+// `launch(first, count, dst)` packs items [first, first + count) into dst, and
+// the host copies one half out while the next is being packed.
+constexpr size_t kStageHalf = sizeof(scmd_ctx::Pinned::stage) / 2;
+template <typename LAUNCH>
+int fetch(scmd_ctx *c, size_t items, size_t item_bytes, void *out, LAUNCH &&launch) {
+    const size_t per = kStageHalf / item_bytes;
+    auto count = [&](size_t k) { return std::min(per, items - k * per); };
+    auto half = [&](size_t k) { return c->pin->stage + (k & 1) * kStageHalf; };
+    const size_t chunks = (items + per - 1) / per;
+    auto enqueue = [&](size_t k) -> hipError_t {
+        hipError_t e = launch(k * per, count(k), half(k));
+        return e != hipSuccess || chunks == 1 ? e : hipEventRecord(c->stage_ev[k & 1], c->stream);
+    };
+    if (chunks > 0) HIP_TRY(c, enqueue(0));
+    for (size_t k = 0; k < chunks; ++k) {
+        if (k + 1 < chunks) HIP_TRY(c, enqueue(k + 1));
+        HIP_TRY(c, chunks == 1 ? hipStreamSynchronize(c->stream) : hipEventSynchronize(c->stage_ev[k & 1]));
+        std::memcpy((char *)out + k * per * item_bytes, half(k), count(k) * item_bytes);
+    }
     return SCMD_OK;
 }
 
@@ -1024,30 +1058,25 @@ int enqueue_steps(scmd_ctx *c, int64_t nsteps) {
     return SCMD_OK;
 }
 
-int copy_state_table(scmd_ctx *c, std::vector<ClusterState> &st) {
-    st.resize(c->nclusters);
-    if (c->nclusters > 0)
-        HIP_TRY(c, hipMemcpy(st.data(), c->d_state.p, st.size() * sizeof(ClusterState), hipMemcpyDeviceToHost));
-    return SCMD_OK;
+// States of the clusters [first, first + count), and the flag: one kernel and
+// one synchronisation.
+int fetch_states(scmd_ctx *c, int first, int count, std::vector<ClusterState> &st) {
+    st.resize(count);
+    constexpr size_t words = sizeof(ClusterState) / sizeof(uint64_t);
+    const uint64_t *src = (const uint64_t *)(c->d_state.p + first);
+    int rc = fetch(c, (size_t)count * words, sizeof(uint64_t), st.data(), [&](size_t a, size_t n, void *dst) {
+        return launch_copy_words(src + a, (uint64_t *)dst, n, c->stream);
+    });
+    return rc != SCMD_OK ? rc : sync_and_check(c);
 }
 
-int copy_aos(scmd_ctx *c, const double4 *src, double *out, const std::vector<double> *scale_per_atom) {
-    std::vector<double4> tmp(c->natoms);
-    if (c->natoms > 0)
-        HIP_TRY(c, hipMemcpy(tmp.data(), src, tmp.size() * sizeof(double4), hipMemcpyDeviceToHost));
-    for (int i = 0; i < c->natoms; ++i) {
-        double s = scale_per_atom ? (*scale_per_atom)[i] : 1.0;
-        if (scale_per_atom) {
-            out[3 * i + 0] = s * tmp[i].x;
-            out[3 * i + 1] = s * tmp[i].y;
-            out[3 * i + 2] = s * tmp[i].z;
-        } else {
-            out[3 * i + 0] = tmp[i].x;
-            out[3 * i + 1] = tmp[i].y;
-            out[3 * i + 2] = tmp[i].z;
-        }
-    }
-    return SCMD_OK;
+// x, y, z of every atom (velocities: times the pending thermostat factor of
+// the atom's cluster).
+int fetch_xyz(scmd_ctx *c, const double4 *src, bool scaled, double *out) {
+    return fetch(c, c->natoms, 3 * sizeof(double), out, [&](size_t a, size_t n, void *dst) {
+        return launch_xyz(src, scaled ? c->d_state.p : nullptr, c->atom_cluster.p, (int)a, (int)n, (double *)dst,
+                          c->stream);
+    });
 }
 
 void release_device(scmd_ctx *c) {
@@ -1076,7 +1105,6 @@ void release_device(scmd_ctx *c) {
     for (auto &fs : c->frames) fs.buf.release();
     c->frames.clear();
     c->diff_seg.release();
-    c->diff_ncentral.release();
     if (c->cells) {
         cell_list_destroy(c->cells);
         c->cells = nullptr;
@@ -1189,18 +1217,14 @@ int scmd_create(scmd_ctx **out, int device, void *hip_stream) {
         c->own_stream = true;
     }
     if ((e = hipStreamCreateWithFlags(&c->cap_stream, hipStreamNonBlocking)) != hipSuccess ||
-        (e = hipHostMalloc((void **)&c->h_flag, sizeof(int), hipHostMallocDefault)) != hipSuccess ||
-        (e = c->d_flag.ensure(1)) != hipSuccess) {
+        (e = hipHostMalloc((void **)&c->pin, sizeof(scmd_ctx::Pinned), hipHostMallocDefault)) != hipSuccess ||
+        (e = hipEventCreateWithFlags(&c->stage_ev[0], hipEventDisableTiming)) != hipSuccess ||
+        (e = hipEventCreateWithFlags(&c->stage_ev[1], hipEventDisableTiming)) != hipSuccess) {
         g_create_error = std::string("context setup: ") + hipGetErrorString(e);
         scmd_destroy(c);
         return SCMD_EDEVICE;
     }
-    *c->h_flag = 0;
-    if ((e = hipMemset(c->d_flag.p, 0, sizeof(int))) != hipSuccess) {
-        g_create_error = std::string("hipMemset: ") + hipGetErrorString(e);
-        scmd_destroy(c);
-        return SCMD_EDEVICE;
-    }
+    c->pin->flag = 0;
     // the device's scratch array (scmd_rdf_noalloc), looked up while the
     // device is current
     void *scr = nullptr;
@@ -1219,12 +1243,13 @@ int scmd_destroy(scmd_ctx *ctx) {
     (void)hipSetDevice(ctx->device);
     if (ctx->stream) (void)hipStreamSynchronize(ctx->stream);
     release_device(ctx);
-    ctx->d_flag.release();
     for (auto &e : ctx->evs) {
         if (e.a) (void)hipEventDestroy(e.a);
         if (e.b) (void)hipEventDestroy(e.b);
     }
-    if (ctx->h_flag) (void)hipHostFree(ctx->h_flag);
+    for (hipEvent_t ev : ctx->stage_ev)
+        if (ev) (void)hipEventDestroy(ev);
+    if (ctx->pin) (void)hipHostFree(ctx->pin);
     if (ctx->cap_stream) (void)hipStreamDestroy(ctx->cap_stream);
     if (ctx->own_stream && ctx->stream) (void)hipStreamDestroy(ctx->stream);
     delete ctx;
@@ -1297,8 +1322,7 @@ int scmd_init_clusters(scmd_ctx *ctx, int n_clusters, const int64_t *offsets, co
             s.lambda = 1.0;
         }
         HIP_TRY(ctx, hipMemcpy(ctx->d_state.p, st.data(), st.size() * sizeof(ClusterState), hipMemcpyHostToDevice));
-        HIP_TRY(ctx, hipMemset(ctx->d_flag.p, 0, sizeof(int)));
-        *ctx->h_flag = 0;
+        ctx->pin->flag = ctx->h_flag = 0;
         ctx->have_clusters = true;
         return SCMD_OK;
     })
@@ -1477,7 +1501,7 @@ int scmd_step_async(scmd_ctx *ctx, int64_t nsteps) {
     if (nsteps < 0) return fail(ctx, SCMD_EINVAL, "nsteps must be >= 0");
     SCMD_GUARD({
         HIP_TRY(ctx, hipSetDevice(ctx->device));
-        if (*ctx->h_flag) return fail(ctx, SCMD_ENONFINITE, "a previous step produced a non-finite energy");
+        if (ctx->h_flag) return fail(ctx, SCMD_ENONFINITE, "a previous step produced a non-finite energy");
         return enqueue_steps(ctx, nsteps);
     })
 }
@@ -1514,16 +1538,13 @@ int scmd_get_energy(scmd_ctx *ctx, int cluster, double out3[3]) {
     if (!ctx->have_forces) return fail(ctx, SCMD_ESTATE, "compute or step first");
     SCMD_GUARD({
         HIP_TRY(ctx, hipSetDevice(ctx->device));
-        rc = sync_and_check(ctx);
-        if (rc != SCMD_OK) return rc;
         std::vector<ClusterState> st;
-        rc = copy_state_table(ctx, st);
+        rc = cluster < 0 ? fetch_states(ctx, 0, ctx->nclusters, st) : fetch_states(ctx, cluster, 1, st);
         if (rc != SCMD_OK) return rc;
         double ep = 0.0, ek = 0.0;
-        for (int k = 0; k < ctx->nclusters; ++k) {
-            if (cluster >= 0 && k != cluster) continue;
-            ep += st[k].epot;
-            ek += st[k].ekin;
+        for (const ClusterState &q : st) {
+            ep += q.epot;
+            ek += q.ekin;
         }
         out3[0] = ep;
         out3[1] = ek;
@@ -1568,17 +1589,12 @@ int scmd_get_samples(scmd_ctx *ctx, int cluster, double *out, int max_samples, i
         if (rc != SCMD_OK) return rc;
         const int64_t held = ctx->sample_cap > 0 ? std::min<int64_t>(ctx->sample_total, ctx->sample_cap) : 0;
         const int64_t take = std::min<int64_t>(held, max_samples);
-        if (take > 0) {
-            std::vector<double> ring((size_t)ctx->sample_cap * ctx->nclusters * 5);
-            HIP_TRY(ctx, hipMemcpy(ring.data(), ctx->d_samples.p, ring.size() * sizeof(double), hipMemcpyDeviceToHost));
-            // the newest `take` samples, oldest first
-            for (int64_t k = 0; k < take; ++k) {
-                const int64_t idx = ctx->sample_total - take + k;  // sample number
-                const size_t slot = (size_t)(idx % ctx->sample_cap);
-                const double *src = ring.data() + (slot * ctx->nclusters + cluster) * 5;
-                for (int q = 0; q < 5; ++q) out[5 * k + q] = src[q];
-            }
-        }
+        const int64_t oldest = ctx->sample_total - take;  // the newest `take` samples, oldest first
+        rc = fetch(ctx, (size_t)take, 5 * sizeof(double), out, [&](size_t a, size_t n, void *dst) {
+            return launch_fetch_samples(ctx->d_samples.p, ctx->sample_cap, ctx->nclusters, cluster,
+                                        oldest + (int64_t)a, (int)n, (double *)dst, ctx->stream);
+        });
+        if (rc != SCMD_OK) return rc;
         *n_out = (int)take;
         if (recorded) *recorded = ctx->sample_total;
         return SCMD_OK;
@@ -1593,12 +1609,10 @@ int scmd_get_temperature(scmd_ctx *ctx, int cluster, double *T_K, int64_t *ndof)
     if (!ctx->have_forces) return fail(ctx, SCMD_ESTATE, "compute or step first");
     SCMD_GUARD({
         HIP_TRY(ctx, hipSetDevice(ctx->device));
-        rc = sync_and_check(ctx);
-        if (rc != SCMD_OK) return rc;
         std::vector<ClusterState> st;
-        rc = copy_state_table(ctx, st);
+        rc = fetch_states(ctx, cluster, 1, st);
         if (rc != SCMD_OK) return rc;
-        *T_K = st[cluster].temp;
+        *T_K = st[0].temp;
         if (ndof) *ndof = ndof_for(ctx->cdesc[cluster].kind, ctx->offsets[cluster + 1] - ctx->offsets[cluster]);
         return SCMD_OK;
     })
@@ -1610,8 +1624,7 @@ int scmd_get_positions(scmd_ctx *ctx, double *out) {
     if (!out && ctx->natoms > 0) return fail(ctx, SCMD_EINVAL, "out is NULL");
     SCMD_GUARD({
         HIP_TRY(ctx, hipSetDevice(ctx->device));
-        HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
-        return copy_aos(ctx, ctx->rp.p, out, nullptr);
+        return fetch_xyz(ctx, ctx->rp.p, false, out);
     })
 }
 
@@ -1621,14 +1634,7 @@ int scmd_get_velocities(scmd_ctx *ctx, double *out) {
     if (!out && ctx->natoms > 0) return fail(ctx, SCMD_EINVAL, "out is NULL");
     SCMD_GUARD({
         HIP_TRY(ctx, hipSetDevice(ctx->device));
-        HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
-        std::vector<ClusterState> st;
-        int rc = copy_state_table(ctx, st);
-        if (rc != SCMD_OK) return rc;
-        std::vector<double> lam(ctx->natoms);
-        for (int k = 0; k < ctx->nclusters; ++k)
-            for (int64_t i = ctx->offsets[k]; i < ctx->offsets[k + 1]; ++i) lam[i] = st[k].lambda;
-        return copy_aos(ctx, ctx->v.p, out, &lam);
+        return fetch_xyz(ctx, ctx->v.p, true, out);
     })
 }
 
@@ -1639,8 +1645,7 @@ int scmd_get_forces(scmd_ctx *ctx, double *out) {
     if (!out && ctx->natoms > 0) return fail(ctx, SCMD_EINVAL, "out is NULL");
     SCMD_GUARD({
         HIP_TRY(ctx, hipSetDevice(ctx->device));
-        HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
-        return copy_aos(ctx, ctx->f.p, out, nullptr);
+        return fetch_xyz(ctx, ctx->f.p, false, out);
     })
 }
 
@@ -1651,10 +1656,9 @@ int scmd_get_density(scmd_ctx *ctx, double *out) {
     if (!out && ctx->natoms > 0) return fail(ctx, SCMD_EINVAL, "out is NULL");
     SCMD_GUARD({
         HIP_TRY(ctx, hipSetDevice(ctx->device));
-        HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
-        if (ctx->natoms > 0)
-            HIP_TRY(ctx, hipMemcpy(out, ctx->rho.p, ctx->natoms * sizeof(double), hipMemcpyDeviceToHost));
-        return SCMD_OK;
+        return fetch(ctx, ctx->natoms, sizeof(double), out, [&](size_t a, size_t n, void *dst) {
+            return launch_copy_words((const uint64_t *)ctx->rho.p + a, (uint64_t *)dst, n, ctx->stream);
+        });
     })
 }
 
@@ -1672,16 +1676,16 @@ int scmd_rdf(scmd_ctx *ctx, int cluster, double r_select, double dr, int nbins, 
     SCMD_GUARD({
         HIP_TRY(ctx, hipSetDevice(ctx->device));
         HIP_TRY(ctx, ctx->rdf_refs.ensure(std::max(n, 1)));
-        HIP_TRY(ctx, ctx->rdf_nref.ensure(1));
-        HIP_TRY(ctx, ctx->rdf_counts.ensure(nbins));
-        HIP_TRY(ctx, launch_rdf(ctx->rp.p, off, n, r_select, dr, nbins, ctx->rdf_refs.p, ctx->rdf_nref.p,
-                                ctx->rdf_counts.p, true, nullptr, ctx->stream));
-        std::vector<unsigned long long> h(nbins);
-        int nr = 0;
-        HIP_TRY(ctx, hipMemcpyAsync(h.data(), ctx->rdf_counts.p, nbins * sizeof(unsigned long long),
-                                    hipMemcpyDeviceToHost, ctx->stream));
-        HIP_TRY(ctx, hipMemcpyAsync(&nr, ctx->rdf_nref.p, sizeof(int), hipMemcpyDeviceToHost, ctx->stream));
-        HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
+        HIP_TRY(ctx, ctx->rdf_counts.ensure((size_t)nbins + 1));
+        HIP_TRY(ctx, launch_rdf(ctx->rp.p, off, n, r_select, dr, nbins, ctx->rdf_refs.p,
+                                (int *)(ctx->rdf_counts.p + nbins), ctx->rdf_counts.p, true, nullptr, ctx->stream));
+        std::vector<unsigned long long> h((size_t)nbins + 1);
+        int rc = fetch(ctx, h.size(), sizeof(uint64_t), h.data(), [&](size_t a, size_t m, void *dst) {
+            return launch_copy_words((const uint64_t *)ctx->rdf_counts.p + a, (uint64_t *)dst, m, ctx->stream);
+        });
+        if (rc != SCMD_OK) return rc;
+        int nr;
+        std::memcpy(&nr, &h[nbins], sizeof(int));
         for (int b = 0; b < nbins; ++b) counts[b] += h[b];
         *n_ref += nr;
         return SCMD_OK;
@@ -1785,18 +1789,14 @@ int scmd_diffusion(scmd_ctx *ctx, int cluster, int64_t first, int nframes, doubl
     if (n < 1) return fail(ctx, SCMD_EINVAL, "empty cluster");
     SCMD_GUARD({
         HIP_TRY(ctx, hipSetDevice(ctx->device));
-        HIP_TRY(ctx, ctx->diff_seg.ensure((size_t)segments + 1));
-        HIP_TRY(ctx, ctx->diff_ncentral.ensure(1));
+        HIP_TRY(ctx, ctx->diff_seg.ensure((size_t)segments));
         const int seg = nframes / segments;
+        // the mean and the count go straight to pinned memory
         HIP_TRY(ctx, launch_diffusion(fs->buf.p, n, fs->cap, first, seg, segments, radius, frame_dt_ps,
-                                      ctx->diff_seg.p, ctx->diff_ncentral.p, ctx->diff_seg.p + segments,
-                                      ctx->stream));
-        double d = 0.0;
-        int nc = 0;
-        HIP_TRY(ctx, hipMemcpyAsync(&d, ctx->diff_seg.p + segments, sizeof(double), hipMemcpyDeviceToHost,
-                                    ctx->stream));
-        HIP_TRY(ctx, hipMemcpyAsync(&nc, ctx->diff_ncentral.p, sizeof(int), hipMemcpyDeviceToHost, ctx->stream));
+                                      ctx->diff_seg.p, &ctx->pin->n_central, &ctx->pin->diffusion, ctx->stream));
         HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
+        const double d = ctx->pin->diffusion;
+        const int nc = ctx->pin->n_central;
         if (nc == 0) return fail(ctx, SCMD_EINVAL, "no atom within radius of the centre of mass");
         *D_A2_per_ps = d;
         *n_central = nc;
@@ -1810,7 +1810,7 @@ int scmd_get_forces_device(scmd_ctx *ctx, double *dev_out) {
     if (!ctx->have_forces) return fail(ctx, SCMD_ESTATE, "compute or step first");
     if (!dev_out && ctx->natoms > 0) return fail(ctx, SCMD_EINVAL, "dev_out is NULL");
     HIP_TRY(ctx, hipSetDevice(ctx->device));
-    HIP_TRY(ctx, launch_aos_from4(ctx->f.p, dev_out, ctx->natoms, ctx->stream));
+    HIP_TRY(ctx, launch_xyz(ctx->f.p, nullptr, nullptr, 0, ctx->natoms, dev_out, ctx->stream));
     return SCMD_OK;
 }
 
@@ -1917,8 +1917,7 @@ int scmd_set_state(scmd_ctx *ctx, const void *buf, size_t bytes) {
         }
         ctx->step = h.step;
         ctx->have_forces = h.have_forces != 0;
-        HIP_TRY(ctx, hipMemset(ctx->d_flag.p, 0, sizeof(int)));
-        *ctx->h_flag = 0;
+        ctx->pin->flag = ctx->h_flag = 0;
         return SCMD_OK;
     })
 }

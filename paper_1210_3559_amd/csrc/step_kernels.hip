@@ -122,14 +122,33 @@ __global__ __launch_bounds__(256) void k_sample(const ClusterState *__restrict__
     o[4] = s.ttarget;
 }
 
-__global__ __launch_bounds__(256) void k_aos_from4(const double4 *__restrict__ src, double *__restrict__ dst,
-                                                   int natoms) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= natoms) return;
-    const double4 q = src[i];
-    dst[3 * (size_t)i + 0] = q.x;
-    dst[3 * (size_t)i + 1] = q.y;
-    dst[3 * (size_t)i + 2] = q.z;
+// What the getters hand out, packed into pinned host memory (or the caller's
+// device memory): consecutive threads write consecutive words, so the bus sees
+// whole lines.
+__global__ __launch_bounds__(256) void k_xyz(const double4 *__restrict__ src, const ClusterState *__restrict__ st,
+                                             const int32_t *__restrict__ atom_cluster, int first, int count,
+                                             double *__restrict__ dst) {
+    const int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (k >= 3 * (int64_t)count) return;
+    const int i = first + (int)(k / 3);
+    const double x = reinterpret_cast<const double *>(src + i)[k % 3];
+    dst[k] = st ? st[atom_cluster[i]].lambda * x : x;
+}
+
+__global__ __launch_bounds__(256) void k_copy_words(const uint64_t *__restrict__ src, uint64_t *__restrict__ dst,
+                                                    int n) {
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i < n) dst[i] = src[i];
+}
+
+// Samples number [first, first + count) of one cluster out of the ring.
+__global__ __launch_bounds__(256) void k_fetch_samples(const double *__restrict__ ring, int cap, int nclusters,
+                                                       int cluster, int64_t first, int count,
+                                                       double *__restrict__ dst) {
+    const int k = blockIdx.x * 256 + threadIdx.x;
+    if (k >= 5 * count) return;
+    const size_t slot = (size_t)((first + k / 5) % cap);
+    dst[k] = ring[(slot * nclusters + cluster) * 5 + k % 5];
 }
 
 }  // namespace
@@ -175,10 +194,28 @@ hipError_t launch_sample(const ClusterState *st, int nclusters, double *ring, in
     return hipGetLastError();
 }
 
-hipError_t launch_aos_from4(const double4 *src, double *dst, int natoms, hipStream_t s) {
-    if (natoms <= 0) return hipSuccess;
+hipError_t launch_xyz(const double4 *src, const ClusterState *st, const int32_t *atom_cluster, int first, int count,
+                      double *dst, hipStream_t s) {
+    if (count <= 0) return hipSuccess;
     (void)hipGetLastError();
-    hipLaunchKernelGGL(k_aos_from4, dim3((natoms + 255) / 256), dim3(256), 0, s, src, dst, natoms);
+    hipLaunchKernelGGL(k_xyz, dim3((unsigned)((3 * (int64_t)count + 255) / 256)), dim3(256), 0, s, src, st,
+                       atom_cluster, first, count, dst);
+    return hipGetLastError();
+}
+
+hipError_t launch_copy_words(const uint64_t *src, uint64_t *dst, size_t n, hipStream_t s) {
+    if (n == 0) return hipSuccess;
+    (void)hipGetLastError();
+    hipLaunchKernelGGL(k_copy_words, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, src, dst, (int)n);
+    return hipGetLastError();
+}
+
+hipError_t launch_fetch_samples(const double *ring, int cap, int nclusters, int cluster, int64_t first, int count,
+                                double *dst, hipStream_t s) {
+    if (count <= 0) return hipSuccess;
+    (void)hipGetLastError();
+    hipLaunchKernelGGL(k_fetch_samples, dim3((5 * count + 255) / 256), dim3(256), 0, s, ring, cap, nclusters, cluster,
+                       first, count, dst);
     return hipGetLastError();
 }
 

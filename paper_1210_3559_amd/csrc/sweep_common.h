@@ -616,6 +616,12 @@ __device__ __forceinline__ void cluster_totals(const ClusterDesc &d, const doubl
     __syncthreads();
 }
 
+// The non-finite flag sits in host memory: a plain store, visible to the host
+// once the stream is synchronised.
+__device__ __forceinline__ void raise_flag(int *flag) {
+    __hip_atomic_store(flag, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // Per-cluster finish, run by one whole workgroup (>= 256 threads): the
 // totals of the tile sums, then temperature and the Berendsen factor.  Every
 // workgroup that runs it for the same cluster and arguments gets the same
@@ -643,7 +649,7 @@ __device__ inline double cluster_finalize(int c, const FinalizeArgs &o, double *
     s.temp = lam * lam * kt.T;
     if (!isfinite(s.epot) || !isfinite(s.ekin)) {
         s.nonfinite = 1;
-        if (writer) atomicOr(o.flag, 1);
+        if (writer) raise_flag(o.flag);
     }
     if (writer) o.st[c] = s;
     return s.lambda;
