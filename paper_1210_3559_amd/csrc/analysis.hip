@@ -15,17 +15,20 @@
 namespace scmd {
 namespace {
 
-constexpr int kSelBlock = 256;
+constexpr int kSelBlock = 1024;
+constexpr int kSelWaves = kSelBlock / 64;
 
 // One workgroup: centre of mass (fixed-order sums), then the indices of the
-// reference atoms in increasing order (compaction by wavefront ballots).
+// reference atoms in increasing order (compaction by wavefront ballots).  It
+// also clears the counts (clear != 0), which saves a launch.
 __global__ __launch_bounds__(kSelBlock) void k_rdf_select(const double4 *__restrict__ rp, int off, int n,
                                                          double r_select, int32_t *__restrict__ refs,
-                                                         int *__restrict__ nref) {
+                                                         int *__restrict__ nref,
+                                                         unsigned long long *__restrict__ counts, int clear) {
 #pragma clang fp contract(off)
-    __shared__ double sh[3 * (kSelBlock / 64)];
-    __shared__ int wave_cnt[kSelBlock / 64];
-    __shared__ int base_sh;
+    __shared__ double sh[3 * kSelWaves];
+    __shared__ int wave_cnt[2][kSelWaves];
+    for (int b = threadIdx.x; b < clear; b += kSelBlock) counts[b] = 0ull;
     const int t = threadIdx.x, lane = t & 63, w = t >> 6;
     double sx = 0.0, sy = 0.0, sz = 0.0;
     for (int i = t; i < n; i += kSelBlock) {
@@ -44,12 +47,18 @@ __global__ __launch_bounds__(kSelBlock) void k_rdf_select(const double4 *__restr
         sh[3 * w + 1] = sy;
         sh[3 * w + 2] = sz;
     }
-    if (t == 0) base_sh = 0;
     __syncthreads();
     const double inv = n > 0 ? 1.0 / (double)n : 0.0;
-    const double cx = ((sh[0] + sh[3]) + (sh[6] + sh[9])) * inv;
-    const double cy = ((sh[1] + sh[4]) + (sh[7] + sh[10])) * inv;
-    const double cz = ((sh[2] + sh[5]) + (sh[8] + sh[11])) * inv;
+    double cx = sh[0], cy = sh[1], cz = sh[2];
+    for (int k = 1; k < kSelWaves; ++k) {
+        cx += sh[3 * k];
+        cy += sh[3 * k + 1];
+        cz += sh[3 * k + 2];
+    }
+    cx *= inv;
+    cy *= inv;
+    cz *= inv;
+    int base = 0;  // references before this round, the same in every thread
     const double rs2 = r_select * r_select;
     for (int i0 = 0; i0 < n; i0 += kSelBlock) {
         const int i = i0 + t;
@@ -61,24 +70,31 @@ __global__ __launch_bounds__(kSelBlock) void k_rdf_select(const double4 *__restr
         }
         const unsigned long long m = __ballot(sel);
         const int before = __popcll(m & ((1ull << lane) - 1ull));
-        if (lane == 0) wave_cnt[w] = __popcll(m);
+        // two buffers in turn: one barrier a round
+        int *cnt = wave_cnt[(i0 / kSelBlock) & 1];
+        if (lane == 0) cnt[w] = __popcll(m);
         __syncthreads();
-        int wbase = base_sh;
-        for (int k = 0; k < w; ++k) wbase += wave_cnt[k];
-        if (sel) refs[wbase + before] = i;
-        __syncthreads();
-        if (t == 0) base_sh += wave_cnt[0] + wave_cnt[1] + wave_cnt[2] + wave_cnt[3];
-        __syncthreads();
+        int at = base;
+        for (int k = 0; k < kSelWaves; ++k) {
+            if (k < w) at += cnt[k];
+            base += cnt[k];
+        }
+        if (sel) refs[at + before] = i;
     }
-    if (t == 0) *nref = base_sh;
+    if (t == 0) *nref = base;
 }
 
 constexpr int kHistBlock = 256;
-constexpr int kRefsPerBlock = 8;
+constexpr int kHistGroups = 1024;  // workgroups at most
 
-// Workgroup b takes reference atoms [8b, 8b + 8) against every atom of the
-// cluster; counts go to a workgroup histogram in LDS, then to the device
-// histogram with 64-bit atomics (nonzero bins only).
+// Workgroup b takes the reference atoms b, b + gridDim.x, ... against every
+// atom of the cluster; counts go to a workgroup histogram in LDS, then to the
+// device histogram with 64-bit atomics (nonzero bins only).  One reference per
+// workgroup fills the chip when only the central atoms are references (Ni2057
+// within 10 A: 8 per workgroup on 48 CUs took 24 us); with many references each
+// workgroup takes several, so the flush stays small.  The bin is
+// floor(d / dr) of the IEEE quotient: the product with 1 / dr decides it unless
+// it comes within rounding of an integer, where the division is done.
 __global__ __launch_bounds__(kHistBlock) void k_rdf_hist(const double4 *__restrict__ rp, int off, int n,
                                                         const int32_t *__restrict__ refs,
                                                         const int *__restrict__ nref, double dr, int nbins,
@@ -87,12 +103,11 @@ __global__ __launch_bounds__(kHistBlock) void k_rdf_hist(const double4 *__restri
     extern __shared__ unsigned int hist[];
     const int t = threadIdx.x;
     const int nr = *nref;
-    const int r0 = blockIdx.x * kRefsPerBlock;
-    if (r0 >= nr) return;  // uniform per workgroup
+    if ((int)blockIdx.x >= nr) return;  // uniform per workgroup
     for (int b = t; b < nbins; b += kHistBlock) hist[b] = 0u;
     __syncthreads();
-    const int r1 = min(nr, r0 + kRefsPerBlock);
-    for (int r = r0; r < r1; ++r) {
+    const double inv_dr = 1.0 / dr, end = (double)nbins;
+    for (int r = blockIdx.x; r < nr; r += gridDim.x) {
         const int i = refs[r];
         const double4 qi = rp[off + i];
         for (int j = t; j < n; j += kHistBlock) {
@@ -100,8 +115,10 @@ __global__ __launch_bounds__(kHistBlock) void k_rdf_hist(const double4 *__restri
             const double4 qj = rp[off + j];
             const double dx = qi.x - qj.x, dy = qi.y - qj.y, dz = qi.z - qj.z;
             const double d = sqrt(dx * dx + dy * dy + dz * dz);
-            const double b = floor(d / dr);
-            if (b < (double)nbins) atomicAdd(&hist[(int)b], 1u);
+            const double q = d * inv_dr;
+            // (also an infinite or subnormal 1 / dr, and NaN, go to the division)
+            const double b = fabs(q - rint(q)) > 1.0e-12 * q + 1.0e-290 && q < 1.0e300 ? floor(q) : floor(d / dr);
+            if (b < end) atomicAdd(&hist[(int)b], 1u);
         }
     }
     __syncthreads();
@@ -109,11 +126,6 @@ __global__ __launch_bounds__(kHistBlock) void k_rdf_hist(const double4 *__restri
         const unsigned int c = hist[b];
         if (c) atomicAdd(&counts[b], (unsigned long long)c);
     }
-}
-
-__global__ void k_fill_u64(unsigned long long *p, int n) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = 0ull;
 }
 
 // Adds the number of reference atoms to a 64-bit device total.
@@ -138,7 +150,7 @@ __global__ void k_add_nref(const int *__restrict__ nref, long long *__restrict__
 // reference q.  The eigenproblem is solved by cyclic Jacobi rotations; a
 // quaternion always gives a proper rotation, so no reflection can appear.
 // ---------------------------------------------------------------------------
-constexpr int kDiffBlock = 256;
+constexpr int kDiffBlock = 1024;
 
 // Sum of K per-thread values over the workgroup in a fixed order (xor
 // butterfly in each wavefront, then the wavefronts in index order); every
@@ -167,6 +179,21 @@ __device__ void block_sum(double (&v)[K], double *sh) {
     }
 }
 
+// 1/x and 1/sqrt(x) from the hardware estimates and two Newton steps (a few
+// 2^-53): one thread works through a chain of these in the eigenproblem, where
+// library division and roots cost several times the latency.
+__device__ __forceinline__ double rcp2(double x) {
+    double y = __builtin_amdgcn_rcp(x);
+    y = __builtin_fma(y, __builtin_fma(-x, y, 1.0), y);
+    return __builtin_fma(y, __builtin_fma(-x, y, 1.0), y);
+}
+__device__ __forceinline__ double rsq2(double x) {
+    double y = __builtin_amdgcn_rsq(x);
+    const double h = 0.5 * x;
+    y = __builtin_fma(y, __builtin_fma(-h * y, y, 0.5), y);
+    return __builtin_fma(y, __builtin_fma(-h * y, y, 0.5), y);
+}
+
 // Rotation matrix (row-major) of the proper rigid motion taking the centred
 // moving frame onto the centred reference, from the cross-covariance S.
 __device__ void horn_rotation(const double S[9], double R[9]) {
@@ -192,13 +219,15 @@ __device__ void horn_rotation(const double S[9], double R[9]) {
                 if (fabs(apq) <= 1e-300) continue;
                 // rotation angle that zeroes A[p][q]: t = tan(phi) is the
                 // smaller root of t^2 + 2 theta t - 1 = 0
-                const double theta = (A[q][q] - A[p][p]) / (2.0 * apq);
+                const double theta = (A[q][q] - A[p][p]) * rcp2(2.0 * apq);
                 double t;
-                if (fabs(theta) > 1e150)
-                    t = 0.5 / theta;
-                else
-                    t = (theta >= 0.0 ? 1.0 : -1.0) / (fabs(theta) + sqrt(theta * theta + 1.0));
-                const double c = 1.0 / sqrt(t * t + 1.0), s = t * c;
+                if (!(fabs(theta) <= 1e150)) {
+                    t = apq / (A[q][q] - A[p][p]);
+                } else {
+                    const double w = theta * theta + 1.0;
+                    t = (theta >= 0.0 ? 1.0 : -1.0) * rcp2(fabs(theta) + w * rsq2(w));
+                }
+                const double c = rsq2(t * t + 1.0), s = t * c;
                 for (int k = 0; k < 4; ++k) {
                     const double akp = A[k][p], akq = A[k][q];
                     A[k][p] = c * akp - s * akq;
@@ -288,9 +317,12 @@ __global__ __launch_bounds__(kDiffBlock) void k_diffusion_segments(const double4
         s18[15] += b2 * r0; s18[16] += b2 * r1; s18[17] += b2 * r2;
     }
     block_sum<18>(s18, sh);
-    if (t == 0) {
-        horn_rotation(s18, rot);
-        horn_rotation(s18 + 9, rot + 9);
+    // both ends at once, on two wavefronts
+    if (t == 0 || t == 64) {
+        double S[9];
+#pragma unroll
+        for (int k = 0; k < 9; ++k) S[k] = t == 0 ? s18[k] : s18[9 + k];
+        horn_rotation(S, t == 0 ? rot : rot + 9);
     }
     __syncthreads();
     double Ra[9], Rb[9];
@@ -342,8 +374,8 @@ __global__ void k_store_frame(const double4 *__restrict__ rp, int off, int n, do
 hipError_t launch_rdf(const double4 *rp, int off, int n, double r_select, double dr, int nbins, int32_t *refs,
                       int *nref, unsigned long long *counts, bool clear, long long *nref_total, hipStream_t s) {
     (void)hipGetLastError();
-    if (clear) hipLaunchKernelGGL(k_fill_u64, dim3((nbins + 255) / 256), dim3(256), 0, s, counts, nbins);
-    hipLaunchKernelGGL(k_rdf_select, dim3(1), dim3(kSelBlock), 0, s, rp, off, n, r_select, refs, nref);
+    hipLaunchKernelGGL(k_rdf_select, dim3(1), dim3(kSelBlock), 0, s, rp, off, n, r_select, refs, nref, counts,
+                       clear ? nbins : 0);
     if (n > 0) {
         const size_t lds = (size_t)nbins * sizeof(unsigned int);
         if (lds > 65536) {
@@ -351,10 +383,9 @@ hipError_t launch_rdf(const double4 *rp, int off, int n, double r_select, double
                                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
             if (e != hipSuccess) return e;
         }
-        // enough workgroups for every atom to be a reference; the surplus
-        // ones return at once
-        hipLaunchKernelGGL(k_rdf_hist, dim3((n + kRefsPerBlock - 1) / kRefsPerBlock), dim3(kHistBlock), lds, s, rp,
-                           off, n, refs, nref, dr, nbins, counts);
+        // workgroups beyond the references return at once
+        hipLaunchKernelGGL(k_rdf_hist, dim3(n < kHistGroups ? n : kHistGroups), dim3(kHistBlock), lds, s, rp, off, n,
+                           refs, nref, dr, nbins, counts);
     }
     if (nref_total) hipLaunchKernelGGL(k_add_nref, dim3(1), dim3(64), 0, s, nref, nref_total);
     return hipGetLastError();
