@@ -49,6 +49,17 @@ struct CellGrid {
     int pad;
 };
 
+// What a sweep's workgroup needs to know of its cell, made by the build for
+// every place in the sweeps' order: one uniform load instead of a chain of five
+// (order, cluster, grid, starts) ahead of the staging.
+struct CellWork {
+    int cell, s0, cnt;  // cell, its first sorted atom, its atoms (0: nothing to do)
+    int m;              // candidates: atoms of the 27 cells
+    int off[9];         // first candidate of each x-row
+    int shift[9];       // sorted atom of candidate p of row r: p + shift[r]
+    int pad[10];
+};
+
 struct CellList {
     int nclusters = 0, natoms = 0, total_cap = 0;
     std::vector<int> cap_base, cap_n;  // per cluster: first cell and cell capacity (host)
@@ -66,6 +77,7 @@ struct CellList {
     int *start = nullptr;         // [total_cap + 1]
     int *cursor = nullptr;        // [total_cap]
     int *corder = nullptr;        // [total_cap] cells in the order the sweeps take them (fullest first)
+    CellWork *work = nullptr;     // [total_cap] the same order
     int *cell_of = nullptr;       // [natoms]
     int *perm = nullptr;          // cell slot -> atom, as scattered
     int *sperm = nullptr;         // cell slot -> atom, sorted by atom index within each cell
@@ -344,7 +356,8 @@ __global__ __launch_bounds__(256) void k_cell_scatter(const int *__restrict__ ce
     if (i < natoms) perm[slot] = i;
 }
 
-// One wavefront per cell: the slot of each atom is its rank (the number of
+// One wavefront per cell, in the sweeps' order: the cell's work record, then
+// the slot of each atom is its rank (the number of
 // atoms of the cell with a smaller index), so sperm lists every cell's atoms
 // in index order whatever order the atomic scatter produced; the sorted
 // positions are gathered at the same time.  Cells larger than the LDS buffer
@@ -355,10 +368,49 @@ constexpr int kOrderLds = 1024;
 __global__ __launch_bounds__(64) void k_cell_order(const int *__restrict__ start, const int *__restrict__ perm,
                                                    int *__restrict__ sperm, const double4 *__restrict__ rp,
                                                    double4 *__restrict__ rs, double4 *__restrict__ ref,
-                                                   int *__restrict__ slot_of, const int *__restrict__ flag) {
+                                                   int *__restrict__ slot_of, const CellGrid *__restrict__ grid,
+                                                   const int *__restrict__ cell_cluster,
+                                                   const int *__restrict__ corder, CellWork *__restrict__ work,
+                                                   const int *__restrict__ flag) {
     __shared__ int sh[kOrderLds];
     if (*flag == 0) return;
-    const int a = start[blockIdx.x], n = start[blockIdx.x + 1] - a;
+    const int cell = corder[blockIdx.x];
+    const CellGrid g = grid[cell_cluster[cell]];
+    const int local_cell = cell - g.base;
+    const int a = start[cell];
+    // cells beyond this build's grid hold nothing
+    const int n = local_cell < g.nx * g.ny * g.nz ? start[cell + 1] - a : 0;
+    {
+        // the x-rows of the neighbourhood, one lane each
+        const int l = threadIdx.x;
+        const int ix = local_cell % g.nx, iy = (local_cell / g.nx) % g.ny, iz = local_cell / (g.nx * g.ny);
+        int ja = 0, jb = 0;
+        if (l < 9 && n > 0) {
+            const int jz = iz + l / 3 - 1, jy = iy + l % 3 - 1;
+            if (jz >= 0 && jz < g.nz && jy >= 0 && jy < g.ny) {
+                const int row = g.base + (jz * g.ny + jy) * g.nx;
+                ja = start[row + max(ix - 1, 0)];
+                jb = start[row + min(ix + 1, g.nx - 1) + 1];
+            }
+        }
+        int end = jb - ja;  // inclusive sum over the rows
+#pragma unroll
+        for (int s = 1; s < 16; s <<= 1) {
+            const int y = __shfl_up(end, s, 64);
+            if (l >= s) end += y;
+        }
+        CellWork *w = work + blockIdx.x;
+        if (l < 9) {
+            w->off[l] = end - (jb - ja);
+            w->shift[l] = ja - (end - (jb - ja));
+        }
+        if (l == 8) w->m = end;
+        if (l == 0) {
+            w->cell = cell;
+            w->s0 = a;
+            w->cnt = n;
+        }
+    }
     if (n == 0) return;
     const bool local = n <= kOrderLds;
     if (local) {
@@ -397,13 +449,12 @@ __global__ __launch_bounds__(64) void k_cell_order(const int *__restrict__ start
 constexpr int kCellWaves = 16;
 constexpr int kCellStage = 2240;  // staged candidates (70 KiB + the queues: two workgroups per CU)
 constexpr int kCellQueue = 128;   // in-range candidates queued per wavefront (< 64 left + 64 new)
+constexpr int kCellFin = 128;     // atoms of a cell whose sums wait in LDS for the finish
+constexpr int kCellAhead = 4;     // list entries per lane fetched an atom ahead (256 of about 300)
 constexpr int kCellNbrCap = 512;  // listed candidates within rc per atom (an atom with more re-tests)
 
 template <int PREC, bool GEN, bool FORCE>
-__global__ __launch_bounds__(64 * kCellWaves) void k_cell_sweep(const CellGrid *__restrict__ grid,
-                                                                const int *__restrict__ corder,
-                                                                const int *__restrict__ cell_cluster,
-                                                                const int *__restrict__ start,
+__global__ __launch_bounds__(64 * kCellWaves, 8) void k_cell_sweep(const CellWork *__restrict__ work,
                                                                 const double4 *__restrict__ rs,
                                                                 const int *__restrict__ sperm,
                                                                 double *__restrict__ fin,
@@ -419,61 +470,58 @@ __global__ __launch_bounds__(64 * kCellWaves) void k_cell_sweep(const CellGrid *
     extern __shared__ double lds_c[];
     double *const lx = lds_c, *const ly = lds_c + kCellStage, *const lz = lds_c + 2 * kCellStage,
                   *const lw = lds_c + 3 * kCellStage;
-    __shared__ int seg_lo[9], seg_len[9], seg_off[10];
-    __shared__ int queue[kCellWaves][kCellQueue];
+    __shared__ uint16_t queue[kCellWaves][kCellQueue];
+    __shared__ double fin_sh[Q * kCellFin];
+    const CellWork &w = work[blockIdx.x];  // uniform: scalar loads
     // A density sweep after a (re)build lists every atom's candidates within
     // rl = rc + skin while it runs; until the next build both sweeps read
     // those lists.  The force sweep ends the build (no later kernel of this
     // evaluation reads the flag).
     const bool build = !FORCE && *flag != 0;
     if (FORCE && blockIdx.x == 0 && threadIdx.x == 0) *flag = 0;
-    const int cell = corder[blockIdx.x];
-    const CellGrid g = grid[cell_cluster[cell]];
-    const int local = cell - g.base;
-    const int s0 = start[cell], cnt = local < g.nx * g.ny * g.nz ? start[cell + 1] - s0 : 0;
+    const int s0 = w.s0, cnt = w.cnt;
     // the cell's slot of the cluster sums (embedding energy, pair energy,
     // v^2), stored by the force sweep; cells without atoms, also those
     // beyond this build's grid, hold zeros
     if (cnt == 0) {  // uniform per workgroup
         if (FORCE && finish && threadIdx.x == 0) {
-            double *const cell_sums = fout.tile_sums + (size_t)cell * kTileSums;
+            double *const cell_sums = fout.tile_sums + (size_t)w.cell * kTileSums;
             cell_sums[0] = 0.0;
             cell_sums[1] = 0.0;
             cell_sums[2] = 0.0;
         }
         return;
     }
-    const int ix = local % g.nx, iy = (local / g.nx) % g.ny, iz = local / (g.nx * g.ny);
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    if (tid < 9) {
-        const int jz = iz + tid / 3 - 1, jy = iy + tid % 3 - 1;
-        int ja = 0, jb = 0;
-        if (jz >= 0 && jz < g.nz && jy >= 0 && jy < g.ny) {
-            const int row = g.base + (jz * g.ny + jy) * g.nx;
-            ja = start[row + max(ix - 1, 0)];
-            jb = start[row + min(ix + 1, g.nx - 1) + 1];
-        }
-        seg_lo[tid] = ja;
-        seg_len[tid] = jb - ja;
-    }
-    __syncthreads();
-    if (tid == 0) {
-        seg_off[0] = 0;
-        for (int r = 0; r < 9; ++r) seg_off[r + 1] = seg_off[r] + seg_len[r];
-    }
-    __syncthreads();
-    const int M = __builtin_amdgcn_readfirstlane(seg_off[9]);
+    const int M = w.m;
     const int M64 = (M + 63) & ~63;  // candidates padded to whole wavefronts
     const bool staged = M64 <= kCellStage;
     // sorted atom of candidate p (p < M)
     auto cand = [&](int p) {
-        int r = 0;
-        while (p >= seg_off[r + 1]) ++r;
-        return seg_lo[r] + (p - seg_off[r]);
+        int k = p + w.shift[0];
+#pragma unroll
+        for (int r = 1; r < 9; ++r) k = p >= w.off[r] ? p + w.shift[r] : k;
+        return k;
     };
     // the record of sorted atom k: position (density sweep), position and P
     // from the density sweep's finish (force sweep)
     auto rec = [&](int k) { return FORCE ? xp[sperm[k]] : rs[k]; };
+    // Loads whose results are needed only later travel with the staging: the
+    // finish's own atom, and the first entries of the wavefront's first list
+    const bool small = cnt <= kCellFin;  // the sums wait in LDS, else in fin
+    int own = 0;
+    if (finish && tid < cnt) own = sperm[s0 + tid];
+    const bool lists = !build && staged;
+    int nlist = 0;
+    unsigned ent[kCellAhead / 2];  // two 16-bit entries each: the sweeps live on 64 registers
+    auto peek = [&](int a) {
+        const int k = s0 + min(a, cnt - 1);
+        nlist = nbr_n[k];
+        const uint16_t *l = nbr + (size_t)k * kCellNbrCap + lane;
+#pragma unroll
+        for (int q = 0; q < kCellAhead; q += 2) ent[q / 2] = l[q * 64] | (unsigned)l[(q + 1) * 64] << 16;
+    };
+    if (lists) peek(wave);
     if (staged) {
         for (int p = tid; p < M; p += 64 * kCellWaves) {
             const double4 q = rec(cand(p));
@@ -492,12 +540,11 @@ __global__ __launch_bounds__(64 * kCellWaves) void k_cell_sweep(const CellGrid *
     }
     __syncthreads();
     const float Af = (float)pc.A;
-    // the own cell lies in the own row (segment 4): atom k is candidate
-    // seg_off[4] + (k - seg_lo[4])
-    const int self0 = seg_off[4] - seg_lo[4];
+    // the own cell lies in the own row (row 4): atom k is candidate k - shift[4]
+    const int self0 = -w.shift[4];
     for (int a = wave; a < cnt; a += kCellWaves) {
         const int k = s0 + a;
-        const double4 qi = rec(k);
+        const double4 qi = staged ? make_double4(lx[self0 + k], ly[self0 + k], lz[self0 + k], lw[self0 + k]) : rec(k);
         const double c_i = -qi.w;
         const float cif = (float)c_i;
         const int self_p = self0 + k;
@@ -514,13 +561,26 @@ __global__ __launch_bounds__(64 * kCellWaves) void k_cell_sweep(const CellGrid *
                 density_pair<PREC, GEN, true, true>(qi.x - q.x, qi.y - q.y, qi.z - q.z, off, acc[0], pc);
         };
         uint16_t *const list = nbr + (size_t)k * kCellNbrCap;
-        const int listed = !build && staged ? __builtin_amdgcn_readfirstlane(nbr_n[k]) : -1;
-        if (!build && staged && listed <= kCellNbrCap) {
+        const int listed = lists ? __builtin_amdgcn_readfirstlane(nlist) : -1;
+        if (lists && listed <= kCellNbrCap) {
             // the density sweep of the last build listed the candidates
             // within rl (same cells; no atom has moved half the skin since,
             // so every pair now closer than rc is among them); lanes take the
-            // entries in the order the queue below handed them out
-            for (int base = 0; base < listed; base += 64) {
+            // entries in the order the queue below handed them out.  The
+            // next atom's first entries travel meanwhile.
+            unsigned now[kCellAhead / 2];
+#pragma unroll
+            for (int q = 0; q < kCellAhead / 2; ++q) now[q] = ent[q];
+            if (a + kCellWaves < cnt) peek(a + kCellWaves);
+#pragma unroll
+            for (int q = 0; q < kCellAhead; ++q) {
+                if (q * 64 < listed) {
+                    const bool v = q * 64 + lane < listed;
+                    const int e = q & 1 ? now[q / 2] >> 16 : now[q / 2] & 0xFFFFu;
+                    pair_terms(staged_cand(v ? e : 0), !v);
+                }
+            }
+            for (int base = kCellAhead * 64; base < listed; base += 64) {
                 const bool v = base + lane < listed;
                 const int e = list[v ? base + lane : base];  // in bounds for every lane
                 pair_terms(staged_cand(v ? e : 0), !v);
@@ -536,7 +596,7 @@ __global__ __launch_bounds__(64 * kCellWaves) void k_cell_sweep(const CellGrid *
             // next build; otherwise (an atom whose list overflowed) it is rc
             // with the pair terms' own expression, so no pair changes side.
             const double rt2 = build ? rl2 : pc.rc2;
-            int *qu = queue[wave];
+            uint16_t *qu = queue[wave];
             int head = 0, qn = 0, total = 0;  // wavefront-uniform
             for (int base = 0; base < M64; base += 64) {
                 const int p = base + lane;
@@ -546,7 +606,7 @@ __global__ __launch_bounds__(64 * kCellWaves) void k_cell_sweep(const CellGrid *
                 const unsigned long long hit = __ballot(in);
                 const int rank = __builtin_amdgcn_mbcnt_hi((unsigned)(hit >> 32),
                                                            __builtin_amdgcn_mbcnt_lo((unsigned)hit, 0u));
-                if (in) qu[(head + qn + rank) & (kCellQueue - 1)] = p;
+                if (in) qu[(head + qn + rank) & (kCellQueue - 1)] = (uint16_t)p;
                 qn += __popcll(hit);
                 if (qn >= 64) {
                     __builtin_amdgcn_wave_barrier();
@@ -569,6 +629,7 @@ __global__ __launch_bounds__(64 * kCellWaves) void k_cell_sweep(const CellGrid *
                 pair_terms(staged_cand(e), !v);
             }
             if (build && lane == 0) nbr_n[k] = total;
+            if (lists && a + kCellWaves < cnt) peek(a + kCellWaves);
         } else {
 #pragma unroll 2
             for (int p = lane; p < M; p += 64) pair_terms(staged ? staged_cand(p) : rec(cand(p)), p == self_p);
@@ -578,32 +639,45 @@ __global__ __launch_bounds__(64 * kCellWaves) void k_cell_sweep(const CellGrid *
         for (int q = 0; q < Q; ++q) acc[q] = wave_total(acc[q]);
         if (lane == 0 && finish) {
 #pragma unroll
-            for (int q = 0; q < Q; ++q) fin[(size_t)k * 4 + q] = acc[q];
+            for (int q = 0; q < Q; ++q) {
+                if (small) fin_sh[q * kCellFin + a] = acc[q];
+                else fin[(size_t)k * 4 + q] = acc[q];
+            }
         }
     }
     if (!finish) return;
+    double4 own_v = make_double4(0, 0, 0, 0);
+    double own_emb = 0.0;
+    if constexpr (FORCE) {
+        if (tid < cnt) {
+            own_v = fout.v[own];
+            own_emb = emb[s0 + tid];
+        }
+    }
     // Finish: thread a takes the cell's atoms a, a + 1024, ... (their sums,
     // stored above by the wavefronts of this workgroup, are visible after
     // the barrier), so the loads of the per-atom epilogue are issued once per
-    // cell rather than on every wavefront's path.
+    // cell rather than on every wavefront's path, the first atoms' ahead.
     __syncthreads();
+    auto sum = [&](int a, int q) { return small ? fin_sh[q * kCellFin + a] : fin[(size_t)(s0 + a) * 4 + q]; };
     if constexpr (!FORCE) {
         // the embedding energies wait per sorted atom for the force sweep,
         // which adds them into the cell's sums (no reduction here: it would
         // hold every wavefront of the cell until the finish is done)
         for (int a = tid; a < cnt; a += 64 * kCellWaves) {
-            const int k = s0 + a;
-            emb[k] = density_atom(sperm[k], fin[(size_t)k * 4], dout, pc);
+            const int k = s0 + a, i = a == tid ? own : sperm[k];
+            const double4 q = staged ? make_double4(lx[self0 + k], ly[self0 + k], lz[self0 + k], 0.0) : dout.rp[i];
+            emb[k] = density_atom_at(i, sum(a, 0), q, dout, pc);
         }
     } else {
         // the cell's sums: each wavefront's in a fixed order (DPP), then the
         // wavefronts' in order
         double se = 0.0, sp = 0.0, sv = 0.0;
         for (int a = tid; a < cnt; a += 64 * kCellWaves) {
-            const int k = s0 + a;
-            const double *t = fin + (size_t)k * 4;
-            se += emb[k];
-            force_atom(sperm[k], t[0], t[1], t[2], t[3], fout, pc, sp, sv);
+            const bool first = a == tid;
+            const int i = first ? own : sperm[s0 + a];
+            se += first ? own_emb : emb[s0 + a];
+            force_atom_v(i, sum(a, 0), sum(a, 1), sum(a, 2), sum(a, 3), first ? own_v : fout.v[i], fout, pc, sp, sv);
         }
         se = wave_total(se);
         sp = wave_total(sp);
@@ -617,12 +691,12 @@ __global__ __launch_bounds__(64 * kCellWaves) void k_cell_sweep(const CellGrid *
         __syncthreads();
         if (threadIdx.x == 0) {
             double e = 0.0, p = 0.0, v2 = 0.0;
-            for (int w = 0; w < kCellWaves; ++w) {
-                e += wsh[0][w];
-                p += wsh[1][w];
-                v2 += wsh[2][w];
+            for (int k = 0; k < kCellWaves; ++k) {
+                e += wsh[0][k];
+                p += wsh[1][k];
+                v2 += wsh[2][k];
             }
-            double *const cell_sums = fout.tile_sums + (size_t)cell * kTileSums;
+            double *const cell_sums = fout.tile_sums + (size_t)w.cell * kTileSums;
             cell_sums[0] = e;
             cell_sums[1] = p;
             cell_sums[2] = v2;
@@ -637,8 +711,8 @@ hipError_t launch_cell_sweep(CellList *cl, const double4 *xp, const DensityOut &
     const dim3 grid(cl->total_cap), block(64 * kCellWaves);
     const size_t lds = kCellStage * sizeof(double4);
 #define SCMD_CELL_ARGS                                                                                          \
-    cl->grid, cl->corder, cl->cell_cluster, cl->start, cl->rs, cl->sperm, cl->fin, cl->emb, cl->nbr, cl->nbr_n, xp, \
-        pc, cl->flag, cl->rl * cl->rl, dout, fout, finish
+    cl->work, cl->rs, cl->sperm, cl->fin, cl->emb, cl->nbr, cl->nbr_n, xp, pc, cl->flag, cl->rl * cl->rl, dout, fout, \
+        finish
     if (precision == SCMD_FP64) {
         if (pc.generic)
             hipLaunchKernelGGL((k_cell_sweep<SCMD_FP64, true, FORCE>), grid, block, lds, s, SCMD_CELL_ARGS);
@@ -671,7 +745,7 @@ void cell_list_destroy(CellList *cl) {
     void *ptrs[] = {cl->grid0, cl->grid,  cl->cell_cluster, cl->count,  cl->start, cl->cursor,
                     cl->cell_of, cl->perm, cl->sperm, cl->box, cl->chunks,
                     cl->atom_cluster, cl->rs, cl->nbr, cl->nbr_n, cl->corder, cl->ref,
-                    cl->slot_of, cl->flag, cl->nbuilds, cl->fin, cl->emb};
+                    cl->slot_of, cl->flag, cl->nbuilds, cl->fin, cl->emb, cl->work};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
     delete cl;
@@ -764,6 +838,7 @@ hipError_t cell_list_plan(CellList *cl, int nclusters, const int64_t *offsets, d
     if ((e = dalloc(&cl->start, base + 1)) != hipSuccess) return e;
     if ((e = dalloc(&cl->cursor, base)) != hipSuccess) return e;
     if ((e = dalloc(&cl->corder, base)) != hipSuccess) return e;
+    if ((e = dalloc(&cl->work, base)) != hipSuccess) return e;
     if ((e = dalloc(&cl->cell_of, natoms)) != hipSuccess) return e;
     if ((e = dalloc(&cl->perm, natoms)) != hipSuccess) return e;
     if ((e = dalloc(&cl->sperm, natoms)) != hipSuccess) return e;
@@ -843,7 +918,7 @@ hipError_t cell_list_build(CellList *cl, const double4 *rp, bool checked, hipStr
     // count and scatter read the previous build's order from sperm before
     // k_cell_order replaces it
     hipLaunchKernelGGL(k_cell_order, dim3(tc), dim3(64), 0, s, cl->start, cl->perm, cl->sperm, rp, cl->rs, cl->ref,
-                       cl->slot_of, cl->flag);
+                       cl->slot_of, cl->grid, cl->cell_cluster, cl->corder, cl->work, cl->flag);
     return hipGetLastError();
 }
 

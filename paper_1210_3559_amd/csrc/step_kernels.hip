@@ -78,30 +78,33 @@ __global__ __launch_bounds__(256) void k_bath_prep(const int32_t *__restrict__ a
 }
 
 // Drift fused with the finish of the previous step of a single cluster:
-// every workgroup reduces the cluster's tile sums itself (same order, so the
-// same thermostat factor in every workgroup) and workgroup 0 stores the
-// cluster state, which saves a launch per step.  CELL: the cell list's
-// check on the drifted positions as well (another launch saved).
+// every workgroup finds the thermostat factor itself from the cluster's v^2
+// sums (same order as the finalize, so the same bits everywhere), which saves a
+// launch per step; without a rescaling thermostat the factor is 1 and no sum is
+// read.  Energies are nobody's business until the run's last step.  CELL: the
+// cell list's check on the drifted positions as well (another launch saved).
 template <bool CELL>
 __global__ __launch_bounds__(256) void k_drift_fin(dev::FinalizeArgs fa, double4 *__restrict__ rp,
                                                    double4 *__restrict__ v, const double4 *__restrict__ f,
                                                    int natoms, double dt, double h, CellCheck cc) {
     __shared__ double sh[12];
     __shared__ double sh_box[6 * (256 / 64)];
-    __shared__ double lam_sh;
-    const double l0 = dev::cluster_finalize(0, fa, sh, blockIdx.x == 0);
-    if (threadIdx.x == 0) lam_sh = l0;
-    __syncthreads();
-    const double lam = lam_sh;
+    const ClusterDesc d0 = fa.cd[0];
+    double lam = 1.0;
+    if (d0.kind == SCMD_BERENDSEN) {
+        double e0, e1, v2, tt;
+        dev::cluster_totals<true>(d0, fa.tile_sums, sh, e0, e1, v2);
+        lam = dev::thermostat_lambda(d0, fa.dt, dev::kinetic_temperature(d0, fa.mass_u, v2).T,
+                                     fa.st[0].step + fa.step_add, &tt);
+    }
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     dev::CellBox b;
     if (i < natoms) {
-        const ClusterDesc &d = fa.cd[0];
         double4 vi = v[i];
         const double4 fi = f[i];
         double4 ri = rp[i];
         // this drift starts step fa.step_add + 1 of the run
-        drift_atom(d, fa.st[0].step + fa.step_add + 1, i - d.off, lam, fa.mass_u, dt, h, ri, vi, fi);
+        drift_atom(d0, fa.st[0].step + fa.step_add + 1, i - d0.off, lam, fa.mass_u, dt, h, ri, vi, fi);
         v[i] = vi;
         rp[i] = ri;
         if constexpr (CELL) dev::cell_check_atom(cc, i, ri, b);
