@@ -17,6 +17,9 @@ constexpr double kBoltzmannEv = 8.617333262145179e-05;
 // exactly zero in double precision (and to inf -> 0 through rsqrt/rcp in
 // single precision), and no sentinel ever meets another at r = 0.
 constexpr double kFar = 1.0e150;
+// The same where two pairs share one reciprocal of their r^2: r^2 ~ 1e151, so
+// the product of two stays finite and u^6 still underflows to zero.
+constexpr double kFarPair = 1.0e75;
 
 // Sutton-Chen constants folded for the kernels.  With u = 1/r:
 //   rho_i      = a^m sum_j u^m                      (density sweep)

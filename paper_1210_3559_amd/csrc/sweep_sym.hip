@@ -51,13 +51,13 @@ struct IGroup {
 };
 
 template <int IPT, typename AT>
-__device__ __forceinline__ void load_group(const SymItem &it, const SymTile *__restrict__ tiles, AT &&at,
+__device__ __forceinline__ void load_group(const SymItem &it, const SymTile *__restrict__ tiles, AT &&at, double far,
                                            IGroup<IPT> &G) {
     const int lane = threadIdx.x & 63;
 #pragma unroll
     for (int p = 0; p < IPT; ++p) {
         G.gi[p] = -1;
-        G.x[p] = G.y[p] = G.z[p] = -kFar;
+        G.x[p] = G.y[p] = G.z[p] = -far;
         G.c[p] = 0.0;
         if (p < it.ng) {
             const SymTile t = tiles[it.t0 + p];
@@ -141,7 +141,7 @@ __global__ __launch_bounds__(64 * NW) void k_sym_force(const SymItem *__restrict
     const int rot0 = wave * RW;
     const float Af = (float)pc.A;
     IGroup<IPT> G;
-    load_group<IPT>(it, tiles, [&](int i) { return xp[i]; }, G);
+    load_group<IPT>(it, tiles, [&](int i) { return xp[i]; }, kFar, G);
     float cif[IPT];
     double fx[IPT], fy[IPT], fz[IPT], eu[IPT];
 #pragma unroll
@@ -335,11 +335,12 @@ __global__ __launch_bounds__(64 * NW) void k_sym_density(const SymItem *__restri
         }
         return rp[i];
     };
-    auto pair_term = [&](double dx, double dy, double dz) {
-        return density_term<PREC, false>(__builtin_fma(dx, dx, __builtin_fma(dy, dy, dz * dz)), pc);
+    auto square = [](double dx, double dy, double dz) {
+        return __builtin_fma(dx, dx, __builtin_fma(dy, dy, dz * dz));
     };
+    auto pair_term = [&](double dx, double dy, double dz) { return density_term<PREC, false>(square(dx, dy, dz), pc); };
     IGroup<IPT> G;
-    load_group<IPT>(it, tiles, position, G);
+    load_group<IPT>(it, tiles, position, kFarPair, G);
     double acc[IPT];
 #pragma unroll
     for (int p = 0; p < IPT; ++p) acc[p] = 0.0;
@@ -349,7 +350,7 @@ __global__ __launch_bounds__(64 * NW) void k_sym_density(const SymItem *__restri
         for (int b = 0; b < IPT; ++b) {
             if (b < it.ng) {
                 const bool own = G.gi[b] >= 0;
-                double xj = own ? G.x[b] : kFar, yj = own ? G.y[b] : kFar, zj = own ? G.z[b] : kFar;
+                double xj = own ? G.x[b] : kFarPair, yj = own ? G.y[b] : kFarPair, zj = own ? G.z[b] : kFarPair;
                 if constexpr (NW > 1) {
                     const int from = (lane - rot0) & 63;
                     xj = __shfl(xj, from, 64);
@@ -385,7 +386,7 @@ __global__ __launch_bounds__(64 * NW) void k_sym_density(const SymItem *__restri
         const int dst = (lane - rot0 - RW) & 63;
         SymTile t = tiles[it.b0];
         auto fetch = [&](const SymTile &u) {
-            return lane < u.ni ? position(u.i0 + lane) : make_double4(kFar, kFar, kFar, 0.0);
+            return lane < u.ni ? position(u.i0 + lane) : make_double4(kFarPair, kFarPair, kFarPair, 0.0);
         };
         auto put = [&](int b, const double4 &q) {
             double *t0 = jtile + (b & 1) * 384;
@@ -393,7 +394,7 @@ __global__ __launch_bounds__(64 * NW) void k_sym_density(const SymItem *__restri
             t0[128 + lane] = t0[192 + lane] = q.y;
             t0[256 + lane] = t0[320 + lane] = q.z;
         };
-        double4 nxt = make_double4(kFar, kFar, kFar, 0.0);
+        double4 nxt = make_double4(kFarPair, kFarPair, kFarPair, 0.0);
         if (wave == 0) nxt = fetch(t);
         if constexpr (NW > 1) {
             if (wave == 0) put(it.b0, nxt);
@@ -416,10 +417,14 @@ __global__ __launch_bounds__(64 * NW) void k_sym_density(const SymItem *__restri
                     zj = jt[256 - k];
                 }
 #pragma unroll
-                for (int p = 0; p < IPT; ++p) {
-                    const double t6 = pair_term(G.x[p] - xj, G.y[p] - yj, G.z[p] - zj);
-                    acc[p] += t6;
-                    rj += t6;
+                for (int p = 0; p < IPT; p += 2) {
+                    double t0, t1;
+                    density_terms<PREC>(square(G.x[p] - xj, G.y[p] - yj, G.z[p] - zj),
+                                        square(G.x[p + 1] - xj, G.y[p + 1] - yj, G.z[p + 1] - zj), t0, t1, pc);
+                    acc[p] += t0;
+                    rj += t0;
+                    acc[p + 1] += t1;
+                    rj += t1;
                 }
                 if constexpr (NW == 1) {
                     xj = ror1(xj);
