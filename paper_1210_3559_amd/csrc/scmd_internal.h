@@ -17,9 +17,10 @@ constexpr double kBoltzmannEv = 8.617333262145179e-05;
 // exactly zero in double precision (and to inf -> 0 through rsqrt/rcp in
 // single precision), and no sentinel ever meets another at r = 0.
 constexpr double kFar = 1.0e150;
-// The same where two pairs share one reciprocal of their r^2: r^2 ~ 1e151, so
-// the product of two stays finite and u^6 still underflows to zero.
-constexpr double kFarPair = 1.0e75;
+// The same where up to four pairs share one reciprocal of their r^2 (density of
+// the symmetric sweeps): r^2 ~ 1e76, so the product of four stays finite; u^6 is
+// 1e-228, lost beside any real term and cleared where there is none.
+constexpr double kFarShared = 3.0e37;
 
 // Sutton-Chen constants folded for the kernels.  With u = 1/r:
 //   rho_i      = a^m sum_j u^m                      (density sweep)

