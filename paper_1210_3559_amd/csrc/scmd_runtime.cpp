@@ -589,7 +589,8 @@ int build_plan(scmd_ctx *c, std::vector<ITile> *tiles_out) {
             c->row_waves = c->tuning.waves_j > 0 ? c->tuning.waves_j : batch || nmax <= 2560 ? 8 : 16;
             return build_row_plan(c, c->tuning.target_items > 0 ? c->tuning.target_items : 256, tiles_out);
         }
-        c->sym = allowed && (c->tuning.pairs == 2 || (c->tuning.pairs == 0 && (batch || nmax > 4096)));
+        c->sym = allowed && (c->tuning.pairs == 2 ||
+                             (c->tuning.pairs == 0 && (batch || nmax > (shape_given ? kRowStageMax : kRowSingleMax))));
         if (c->sym) {
             // Tiles per wavefront group and items per sweep.  More tiles per
             // group mean fewer moves per pair but fewer, longer items; us per

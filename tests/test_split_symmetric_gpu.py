@@ -55,3 +55,21 @@ def test_folded_drift_follows_the_oracle(ipt, kinds):
         assert np.abs(r[off[k]:off[k + 1]] - r_ref).max() < 1e-10
         assert np.abs(v[off[k]:off[k + 1]] - v_ref).max() < 1e-11
         assert e[k] == pytest.approx(log[-1, 0], rel=1e-10, abs=1e-300)
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("n", [3072, 3073, 4096])
+def test_default_plan_around_the_row_limits(n, precision):
+    # a single cluster leaves the row sweeps for the symmetric ones above 3072
+    # atoms in double, above 4096 in mixed precision
+    rng = np.random.default_rng(n)
+    p = inputs.jitter(inputs.fcc_exact(n), 0.05, rng)
+    print(f"[split-sym] default plan n={n} {precision}", flush=True)
+    with scmd.Simulation([0, n], p, None, precision=precision) as sim:
+        sim.compute()
+        f, rho, e = sim.forces(), sim.density(), sim.energy()[0]
+    f_ref, rho_ref, site = oracle.forces(p, nthreads=NT)
+    tol = 1e-10 if precision == "fp64" else 1e-5
+    assert np.linalg.norm(f - f_ref) <= tol * np.linalg.norm(f_ref)
+    np.testing.assert_allclose(rho, rho_ref, rtol=tol, atol=0)
+    assert e == pytest.approx(site.sum(), rel=tol)
