@@ -239,7 +239,7 @@ __global__ __launch_bounds__(64 * NW) void k_sym_force(const SymItem *__restrict
             }
             const double2 *jt = jtile + (NW > 1 ? (b & 1) * 256 + lane + 64 - rot0 : 0);
             double gx = 0.0, gy = 0.0, gz = 0.0;
-#pragma unroll 2
+#pragma unroll(IPT == 2 ? 4 : 2)
             for (int k = 0; k < RW; ++k) {
                 if constexpr (NW > 1) {
                     const double2 q0 = jt[-k], q1 = jt[128 - k];
@@ -410,7 +410,7 @@ __global__ __launch_bounds__(64 * NW) void k_sym_density(const SymItem *__restri
             }
             const double *jt = jtile + (NW > 1 ? (b & 1) * 384 + lane + 64 - rot0 : 0);
             double rj = 0.0;
-#pragma unroll 2
+#pragma unroll(IPT == 2 ? 4 : 2)
             for (int k = 0; k < RW; ++k) {
                 if constexpr (NW > 1) {
                     xj = jt[-k];
