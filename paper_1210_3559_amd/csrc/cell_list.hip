@@ -16,12 +16,13 @@
 //           than the cluster's cell capacity, so an escaping atom makes cells
 //           coarser, never wrong); its cell; integer atomics count atoms per
 //           cell (one atomic per cell and wavefront);
-//   scan    exclusive prefix sum of the counts (one workgroup), which clears
-//           the counts and resets the boxes for the next build;
-//   scatter per atom: a slot in its cell (atomic cursor, again one atomic
-//           per cell and wavefront);
-//   order   per cell: every atom's slot becomes its rank by atom index, so
-//           the cell-sorted order is deterministic; positions are gathered.
+//   scatter exclusive prefix sum of the counts (by every workgroup for itself;
+//           a launch of its own for very many cells), then per atom a slot in
+//           its cell (atomic cursor, again one atomic per cell and wavefront);
+//           resets the boxes for the next check;
+//   order   per cell: its work record; every atom's slot becomes its rank by
+//           atom index, so the cell-sorted order is deterministic; positions
+//           are gathered; the counts are cleared for the next build.
 // Sweeps: one workgroup per cell (fullest cells first); the candidates of
 // the 27 neighbouring cells (9 contiguous x-rows of the sorted arrays) are
 // staged in LDS, and each wavefront takes the cell's atoms one at a time
@@ -245,28 +246,21 @@ __global__ __launch_bounds__(256) void k_cell_count(const CellGrid *__restrict__
 constexpr int kScanBlock = 1024;
 
 constexpr int kOrderBins = 256;
+constexpr int kScanLds = 12288;  // cells whose starts a scattering workgroup keeps in LDS (48 KiB)
 
-// Exclusive prefix sum of count[0..total) into start[0..total] (and cursor),
-// one workgroup: per-thread chunk sums, wavefront scans, a scan of the
-// wavefront totals.  Also the order in which the sweeps take the cells:
-// fullest first (a counting sort on the atom count, clamped at 255), so that
-// the longest workgroups start first and the short ones fill in behind them
-// (the order within one count depends on timing; each cell's sums do not
-// depend on which workgroup takes it).  The counts are cleared behind the
-// read and the bounding boxes reset, ready for the next build.
-__global__ __launch_bounds__(kScanBlock) void k_cell_scan(int *__restrict__ count, int *__restrict__ start,
-                                                          int *__restrict__ cursor, int *__restrict__ corder,
-                                                          int total, long long *__restrict__ box, int nclusters,
-                                                          const int *__restrict__ flag,
-                                                          unsigned long long *__restrict__ nbuilds) {
+// Exclusive prefix sum of count[0..total) by one workgroup of kScanBlock threads
+// (per-thread chunk sums, wavefront scans, a scan of the wavefront totals), into
+// `starts` (LDS) when given and, with `store`, into start[0..total].  With
+// `store` also the order in which the sweeps take the cells: fullest first (a
+// counting sort on the atom count, clamped at 255), so that the longest
+// workgroups start first and the short ones fill in behind them (the order
+// within one count depends on timing; each cell's sums do not depend on which
+// workgroup takes it).
+__device__ __forceinline__ void cell_scan(const int *__restrict__ count, int total, int *starts, bool store,
+                                          int *__restrict__ start, int *__restrict__ corder) {
     __shared__ int wsum[kScanBlock / 64];
     __shared__ int bins[kOrderBins];
     const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-    if (*flag == 0) {  // no build: only reset the boxes for the next check
-        for (int k = t; k < 6 * nclusters; k += kScanBlock) box[k] = ord_encode((k % 6) < 3 ? INFINITY : -INFINITY);
-        return;
-    }
-    if (t == 0) *nbuilds += 1ull;
     for (int q = t; q < kOrderBins; q += kScanBlock) bins[q] = 0;
     const int per = (total + kScanBlock - 1) / kScanBlock;
     const int a = min(total, t * per), b = min(total, a + per);
@@ -293,15 +287,20 @@ __global__ __launch_bounds__(kScanBlock) void k_cell_scan(int *__restrict__ coun
     int run = x - s + (w > 0 ? wsum[w - 1] : 0);
     for (int k = a; k < b; ++k) {
         const int c = count[k];
-        start[k] = run;
-        cursor[k] = run;
+        if (starts) starts[k] = run;
+        if (store) start[k] = run;
         run += c;
+        if (!store) continue;
         if (c == 0) {  // the empty cells (most of the capacity): one LDS atomic per wavefront
             const unsigned long long zm = __ballot(1);
             if (lane == __builtin_ctzll(zm)) atomicAdd(&bins[kOrderBins - 1], __popcll(zm));
         } else {
             atomicAdd(&bins[kOrderBins - 1 - min(c, kOrderBins - 1)], 1);
         }
+    }
+    if (!store) {
+        __syncthreads();
+        return;
     }
     if (t == kScanBlock - 1) start[total] = wsum[kScanBlock / 64 - 1];
     __syncthreads();
@@ -338,22 +337,51 @@ __global__ __launch_bounds__(kScanBlock) void k_cell_scan(int *__restrict__ coun
             pos = atomicAdd(&bins[kOrderBins - 1 - min(c, kOrderBins - 1)], 1);
         }
         corder[pos] = k;
-        count[k] = 0;
     }
-    for (int k = t; k < 6 * nclusters; k += kScanBlock) box[k] = ord_encode((k % 6) < 3 ? INFINITY : -INFINITY);
+}
+
+// The scan as a launch of its own, for grids of more than kScanLds cells (100
+// clusters of 2243 atoms: 385 us per step, 684 when rebuilt every step).
+__global__ __launch_bounds__(kScanBlock) void k_cell_scan(const int *__restrict__ count, int *__restrict__ start,
+                                                          int *__restrict__ corder, int total,
+                                                          const int *__restrict__ flag) {
+    if (*flag == 0) return;
+    cell_scan(count, total, nullptr, true, start, corder);
 }
 
 // Per atom, in the previous build's cell order as for the counts: a slot in
-// its cell (which slot depends on timing; k_cell_order ranks them).
-__global__ __launch_bounds__(256) void k_cell_scatter(const int *__restrict__ cell_of, const int *__restrict__ prev,
-                                                      int *__restrict__ cursor, int *__restrict__ perm, int natoms,
-                                                      const int *__restrict__ flag) {
+// its cell (which slot depends on timing; k_cell_order ranks them).  SCAN: every
+// workgroup scans the counts for itself, the first one stores the result, while
+// the starts fit the LDS of two workgroups per CU (kScanLds).  A launch of its own
+// for the scan costs 4.7 us on every step, with or without a build, and bounds it:
+// us per step without and with SCAN, lists reused | rebuilt every step, 500 atoms
+// 32.8 -> 31.4 | 44.0 -> 43.3, 48,077 atoms 87.6 -> 85.3 | 129.4 -> 126.1, 98
+// clusters of 13 atoms (12,250 cells) 46.3 -> 43.6 | 73.3 -> 63.3.  Every launch
+// leaves the boxes reset for the next check.
+template <bool SCAN>
+__global__ __launch_bounds__(kScanBlock) void k_cell_scatter(const int *__restrict__ count, int *__restrict__ start,
+                                                             int *__restrict__ corder, int total,
+                                                             const int *__restrict__ cell_of,
+                                                             const int *__restrict__ prev, int *__restrict__ cursor,
+                                                             int *__restrict__ perm, int natoms,
+                                                             long long *__restrict__ box, int nclusters,
+                                                             unsigned long long *__restrict__ nbuilds,
+                                                             const int *__restrict__ flag) {
+    extern __shared__ int starts_sh[];
+    if (blockIdx.x == 0)
+        for (int k = threadIdx.x; k < 6 * nclusters; k += kScanBlock)
+            box[k] = ord_encode((k % 6) < 3 ? INFINITY : -INFINITY);
     if (*flag == 0) return;
+    if (blockIdx.x == 0 && threadIdx.x == 0) *nbuilds += 1ull;
+    if constexpr (SCAN) {
+        cell_scan(count, total, starts_sh, blockIdx.x == 0, start, corder);
+        __syncthreads();
+    }
     const int t = blockIdx.x * blockDim.x + threadIdx.x;
     const int i = t < natoms ? prev[t] : natoms;
     const int cell = i < natoms ? cell_of[i] : -1;
     const int slot = wave_cell_add<true>(cursor, cell, threadIdx.x & 63);
-    if (i < natoms) perm[slot] = i;
+    if (i < natoms) perm[(SCAN ? starts_sh[cell] : start[cell]) + slot] = i;
 }
 
 // One wavefront per cell, in the sweeps' order: the cell's work record, then
@@ -371,10 +399,12 @@ __global__ __launch_bounds__(64) void k_cell_order(const int *__restrict__ start
                                                    int *__restrict__ slot_of, const CellGrid *__restrict__ grid,
                                                    const int *__restrict__ cell_cluster,
                                                    const int *__restrict__ corder, CellWork *__restrict__ work,
+                                                   int *__restrict__ count, int *__restrict__ cursor,
                                                    const int *__restrict__ flag) {
     __shared__ int sh[kOrderLds];
     if (*flag == 0) return;
     const int cell = corder[blockIdx.x];
+    if (threadIdx.x == 0) count[cell] = cursor[cell] = 0;  // for the next build
     const CellGrid g = grid[cell_cluster[cell]];
     const int local_cell = cell - g.base;
     const int a = start[cell];
@@ -848,8 +878,11 @@ hipError_t cell_list_plan(CellList *cl, int nclusters, const int64_t *offsets, d
         (e = hipMemcpy(cl->chunks, chunks.data(), chunks.size() * sizeof(int4), hipMemcpyHostToDevice)) != hipSuccess)
         return e;
     hipLaunchKernelGGL(k_cell_box_reset, dim3((6 * nclusters + 63) / 64), dim3(64), 0, 0, cl->box, nclusters);
-    // the counts start at zero; each build's scan clears them again
-    if (base > 0) hipLaunchKernelGGL(k_cell_clear, dim3((base + 255) / 256), dim3(256), 0, 0, cl->count, base);
+    // the counts and cursors start at zero; each build's last kernel clears them again
+    if (base > 0) {
+        hipLaunchKernelGGL(k_cell_clear, dim3((base + 255) / 256), dim3(256), 0, 0, cl->count, base);
+        hipLaunchKernelGGL(k_cell_clear, dim3((base + 255) / 256), dim3(256), 0, 0, cl->cursor, base);
+    }
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if ((e = hipDeviceSynchronize()) != hipSuccess) return e;
     if ((e = dalloc(&cl->atom_cluster, natoms)) != hipSuccess) return e;
@@ -910,15 +943,23 @@ hipError_t cell_list_build(CellList *cl, const double4 *rp, bool checked, hipStr
     if (na > 0)
         hipLaunchKernelGGL(k_cell_count, dim3((na + 255) / 256), dim3(256), 0, s, cl->grid0, cl->grid, cl->box, cl->rl,
                            cl->atom_cluster, rp, cl->sperm, cl->cell_of, cl->count, na, cl->flag);
-    hipLaunchKernelGGL(k_cell_scan, dim3(1), dim3(kScanBlock), 0, s, cl->count, cl->start, cl->cursor, cl->corder, tc,
-                       cl->box, cl->nclusters, cl->flag, cl->nbuilds);
-    if (na > 0)
-        hipLaunchKernelGGL(k_cell_scatter, dim3((na + 255) / 256), dim3(256), 0, s, cl->cell_of, cl->sperm, cl->cursor,
-                           cl->perm, na, cl->flag);
+    const dim3 blocks(std::max(1, (na + kScanBlock - 1) / kScanBlock));
+    if (tc <= kScanLds) {
+        hipLaunchKernelGGL(k_cell_scatter<true>, blocks, dim3(kScanBlock), tc * sizeof(int), s, cl->count, cl->start,
+                           cl->corder, tc, cl->cell_of, cl->sperm, cl->cursor, cl->perm, na, cl->box, cl->nclusters,
+                           cl->nbuilds, cl->flag);
+    } else {
+        hipLaunchKernelGGL(k_cell_scan, dim3(1), dim3(kScanBlock), 0, s, cl->count, cl->start, cl->corder, tc,
+                           cl->flag);
+        hipLaunchKernelGGL(k_cell_scatter<false>, blocks, dim3(kScanBlock), 0, s, cl->count, cl->start, cl->corder, tc,
+                           cl->cell_of, cl->sperm, cl->cursor, cl->perm, na, cl->box, cl->nclusters, cl->nbuilds,
+                           cl->flag);
+    }
     // count and scatter read the previous build's order from sperm before
     // k_cell_order replaces it
     hipLaunchKernelGGL(k_cell_order, dim3(tc), dim3(64), 0, s, cl->start, cl->perm, cl->sperm, rp, cl->rs, cl->ref,
-                       cl->slot_of, cl->grid, cl->cell_cluster, cl->corder, cl->work, cl->flag);
+                       cl->slot_of, cl->grid, cl->cell_cluster, cl->corder, cl->work, cl->count, cl->cursor,
+                       cl->flag);
     return hipGetLastError();
 }
 
