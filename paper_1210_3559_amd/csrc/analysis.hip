@@ -85,7 +85,7 @@ __global__ __launch_bounds__(kSelBlock) void k_rdf_select(const double4 *__restr
 }
 
 constexpr int kHistBlock = 256;
-constexpr int kHistGroups = 1024;  // workgroups at most
+constexpr int kHistGroups = 1024;  // workgroups, while a workgroup's 32-bit bins hold all their pairs
 
 // Workgroup b takes the reference atoms b, b + gridDim.x, ... against every
 // atom of the cluster; counts go to a workgroup histogram in LDS, then to the
@@ -383,8 +383,13 @@ hipError_t launch_rdf(const double4 *rp, int off, int n, double r_select, double
                                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
             if (e != hipSuccess) return e;
         }
-        // workgroups beyond the references return at once
-        hipLaunchKernelGGL(k_rdf_hist, dim3(n < kHistGroups ? n : kHistGroups), dim3(kHistBlock), lds, s, rp, off, n,
+        // Every reference may add n - 1 pairs to one bin: from 2,097,153 atoms
+        // on, 1024 workgroups no longer share out the references finely enough.
+        // Workgroups beyond the references return at once.
+        const unsigned most = 0xFFFFFFFFu / (unsigned)(n > 1 ? n - 1 : 1);  // references per workgroup
+        const unsigned groups = (unsigned)(n - 1) / most + 1;
+        const unsigned usual = n < kHistGroups ? n : kHistGroups;
+        hipLaunchKernelGGL(k_rdf_hist, dim3(groups > usual ? groups : usual), dim3(kHistBlock), lds, s, rp, off, n,
                            refs, nref, dr, nbins, counts);
     }
     if (nref_total) hipLaunchKernelGGL(k_add_nref, dim3(1), dim3(64), 0, s, nref, nref_total);

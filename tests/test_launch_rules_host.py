@@ -1,0 +1,21 @@
+"""What the host side launches, recorded without a GPU: grids against the limits
+of their kernels, and which kernels a call takes."""
+import recorder
+
+
+def test_histogram_bins_of_a_workgroup_cannot_overflow():
+    # each of a workgroup's references adds up to n - 1 pairs to one 32-bit bin
+    got = recorder.run("""
+result = []
+for n in (1, 2, 1000, 1024, 1025, 48077, 2097152, 2097153, 3000000, 6000000):
+    pos = np.zeros((n, 3))
+    pos[:, 0] = np.arange(n)
+    with scmd.Simulation([0, n], pos) as sim:
+        records()
+        sim.rdf(0, 1.0, 16)
+        result.append([n] + [r[2] for r in records() if r[0] == "launch" and "k_rdf_hist" in r[1]])
+""")
+    for n, groups in got:
+        per_group = -(-n // groups)
+        assert per_group * (n - 1) < 2**32, (n, groups)
+    assert dict(map(tuple, got))[48077] == 1024
