@@ -53,7 +53,6 @@ hipError_t scratch_address(int device, void **out) {
 }
 
 constexpr int kGraphSteps = 32;  // steps per captured graph
-constexpr int kResidentEval = 96;
 constexpr int64_t kResidentSteps = 1024;  // steps per launch of a resident run (a few ms)
 
 struct EvPair {
@@ -862,9 +861,9 @@ hipError_t enqueue_sweeps(scmd_ctx *c, hipStream_t s, bool capturing, int advanc
 // rho, F, energies at the current positions; advance = 1 also kicks and
 // runs the thermostat (second half of a step).
 hipError_t enqueue_forces(scmd_ctx *c, hipStream_t s, bool capturing, int advance) {
-    // one evaluation of more than kResidentEval atoms is faster on the whole
-    // chip (147 atoms with its copies: 82.9 us on the row sweeps, 85.3 here)
-    if (runs_resident(c) && !advance && c->row_nmax <= kResidentEval)
+    // The kernel of the runs, so that an evaluation between two runs has the
+    // bits of the run's own forces and leaves the trajectory as it is.
+    if (runs_resident(c) && !advance)
         return launch_resident(buffers(c), step_args(c, 0), c->nclusters, c->row_nmax, 0, c->pc, c->precision, s);
     hipError_t e = enqueue_sweeps(c, s, capturing, advance);
     if (e != hipSuccess) return e;

@@ -19,3 +19,20 @@ for n in (1, 2, 1000, 1024, 1025, 48077, 2097152, 2097153, 3000000, 6000000):
         per_group = -(-n // groups)
         assert per_group * (n - 1) < 2**32, (n, groups)
     assert dict(map(tuple, got))[48077] == 1024
+
+
+def test_an_evaluation_takes_the_kernels_of_the_run():
+    # so that compute() between two calls of step() changes no bit of what follows
+    got = recorder.run("""
+result = []
+for sizes in ([13], [96], [97], [147], [152], [153], [2243], [3501], [150] * 16, [96] * 16):
+    off = np.concatenate([[0], np.cumsum(sizes)])
+    with scmd.Simulation(off, np.concatenate([cluster(n) for n in sizes])) as sim:
+        sim.compute()
+        evaluation = sorted({r[1] for r in records()})
+        sim.step(1)
+        result.append([sizes, evaluation, sorted({r[1] for r in records()})])
+""")
+    family = lambda names: {f for n in names for f in ("k_resident", "k_row_", "k_sym_") if f in n}
+    for sizes, evaluation, run in got:
+        assert family(evaluation) == family(run) and len(family(run)) == 1, sizes
