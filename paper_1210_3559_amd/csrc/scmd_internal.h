@@ -250,12 +250,19 @@ hipError_t launch_bath_prep(const StepArgs &a, const int32_t *atom_cluster, cons
 // workgroup, in one launch (0: rho, F and energies at the current positions);
 // the cluster states are complete afterwards.  All pairs, every cluster at most
 // kResidentMax atoms.
-// kResidentMax is what one CU's LDS holds; a few clusters alone gain up to
-// kResidentFew atoms.  us per step, row sweeps / resident: 13 atoms 9.8 / 1.4,
-// 55: 10.2 / 3.6, 100 (bath): 11.1 / 6.6, 147: 10.3 / 9.1, 160: 10.3 / 10.7; 200
-// clusters of 150 22.6 / 9.5, 600 of 55 18.5 / 6.8, 20 of 147 11.9 / 10.3.
+// A step takes one CU the same time however many clusters there are, up to one per
+// CU; the row sweeps take 9 to 10.5 us for a few clusters and grow with the pairs.
+// us per step, row sweeps / resident: 13 atoms 9.3 / 1.3, 55: 9.4 / 3.0, 100: 8.8 /
+// 5.8 (bath 9.9 / 6.8), 130: 9.1 / 8.3; from 137 to 152 atoms they are about even
+// (140: 9.1 / 9.5, 147: 9.6 / 9.3, 152: 9.1 / 9.5, mixed 9.1 / 9.0) and 20 clusters
+// of 147 take 11.1 / 9.4, 200 of 150 22.8 / 9.8, 600 of 55 18.8 / 7.1.  Above
+// kResidentFew the sweeps are faster until a batch has the pairs of about 43
+// clusters as large as its largest (kResidentPairs n^2): 16 of 190 10.3 / 13.5, 40:
+// 13.0 / 13.5, 48: 14.4 / 13.5, 64: 15.2 / 13.4; one of 190 with 511 of 55 18.3 /
+// 13.5.  kResidentMax is what one CU's LDS holds.
 constexpr int kResidentMax = 190;
 constexpr int kResidentFew = 152;
+constexpr double kResidentPairs = 21.0;
 hipError_t launch_resident(const SweepBuffers &B, const StepArgs &a, int nclusters, int nmax, int nsteps,
                            const PotConst &pc, int precision, hipStream_t s);
 

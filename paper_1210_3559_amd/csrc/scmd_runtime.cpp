@@ -579,7 +579,8 @@ int build_plan(scmd_ctx *c, std::vector<ITile> *tiles_out) {
             c->row = true;
             // (kResidentMax: both sides measured)
             c->resident = c->tuning.pairs == 0 && c->natoms > 0 &&
-                          nmax <= (c->nclusters >= 16 ? kResidentMax : kResidentFew);
+                          (nmax <= kResidentFew ||
+                           (nmax <= kResidentMax && upairs >= kResidentPairs * (double)nmax * (double)nmax));
             // one workgroup per CU from about 2560 atoms on (two no longer fit
             // the LDS), so the runs have to divide the groups evenly: 16
             // wavefronts do where 8 leave a fifth of them idle or need a

@@ -36,3 +36,19 @@ for sizes in ([13], [96], [97], [147], [152], [153], [2243], [3501], [150] * 16,
     family = lambda names: {f for n in names for f in ("k_resident", "k_row_", "k_sym_") if f in n}
     for sizes, evaluation, run in got:
         assert family(evaluation) == family(run) and len(family(run)) == 1, sizes
+
+
+def test_batches_above_152_atoms_stay_resident_only_when_they_fill_the_chip():
+    # one workgroup per cluster takes as long for 16 clusters as for 256; the row
+    # sweeps of a few are faster (16 x 190 atoms 10.3 us per step against 13.5)
+    got = recorder.run("""
+result = []
+for sizes in ([152] * 2, [152] * 16, [153] * 16, [190] * 16, [190] + [13] * 15, [190] * 42, [190] * 48, [191] * 48,
+              [190] + [55] * 511):
+    off = np.concatenate([[0], np.cumsum(sizes)])
+    with scmd.Simulation(off, np.concatenate([cluster(n) for n in sizes])) as sim:
+        records()
+        sim.step(1)
+        result.append([any("k_resident" in r[1] for r in records())])
+""")
+    assert [r[0] for r in got] == [True, True, False, False, False, False, True, False, True]
