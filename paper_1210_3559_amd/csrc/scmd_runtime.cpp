@@ -585,8 +585,9 @@ int build_plan(scmd_ctx *c, std::vector<ITile> *tiles_out) {
             // the LDS), so the runs have to divide the groups evenly: 16
             // wavefronts do where 8 leave a fifth of them idle or need a
             // second round (2600 atoms 32.3 us per step at 8, 21.1 at 16; 2243
-            // 17.7 / 18.2)
-            c->row_waves = c->tuning.waves_j > 0 ? c->tuning.waves_j : batch || nmax <= 2560 ? 8 : 16;
+            // 17.7 / 18.2); row sweeps asked for have 8 unless told otherwise
+            c->row_waves = c->tuning.waves_j > 0 ? c->tuning.waves_j
+                                                 : batch || c->tuning.pairs == 3 || nmax <= 2560 ? 8 : 16;
             return build_row_plan(c, c->tuning.target_items > 0 ? c->tuning.target_items : 256, tiles_out);
         }
         c->sym = allowed && (c->tuning.pairs == 2 ||

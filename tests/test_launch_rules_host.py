@@ -52,3 +52,16 @@ for sizes in ([152] * 2, [152] * 16, [153] * 16, [190] * 16, [190] + [13] * 15, 
         result.append([any("k_resident" in r[1] for r in records())])
 """)
     assert [r[0] for r in got] == [True, True, False, False, False, False, True, False, True]
+
+
+def test_row_sweeps_on_request_have_eight_wavefronts_unless_told_otherwise():
+    got = recorder.run("""
+result = []
+for n in (700, 2560, 2561, 4096):
+    for tuning in (dict(pairs=3), dict(pairs=3, waves_j=8), dict(pairs=3, waves_j=16)):
+        with scmd.Simulation([0, n], cluster(n), tuning=tuning) as sim:
+            records()
+            sim.step(1)
+            result.append([n, tuning.get("waves_j", 0), sorted({r[3] // 64 for r in records() if r[0] == "launch" and "k_row" in r[1]})])
+""")
+    assert all(waves == [asked or 8] for _, asked, waves in got), got
