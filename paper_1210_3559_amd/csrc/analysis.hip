@@ -378,11 +378,7 @@ hipError_t launch_rdf(const double4 *rp, int off, int n, double r_select, double
                        clear ? nbins : 0);
     if (n > 0) {
         const size_t lds = (size_t)nbins * sizeof(unsigned int);
-        if (lds > 65536) {
-            hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_rdf_hist),
-                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-            if (e != hipSuccess) return e;
-        }
+        if (hipError_t e = allow_lds(k_rdf_hist, lds, kRdfMaxBins * sizeof(unsigned int)); e != hipSuccess) return e;
         // Every reference may add n - 1 pairs to one bin: from 2,097,153 atoms
         // on, 1024 workgroups no longer share out the references finely enough.
         // Workgroups beyond the references return at once.

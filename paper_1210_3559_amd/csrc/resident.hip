@@ -300,8 +300,7 @@ __global__ __launch_bounds__(kResBlock, 4) void k_resident(ResidentArgs o, PotCo
 template <int PREC, bool GEN, int S>
 hipError_t launch_s(const ResidentArgs &o, int nclusters, int nmax, const PotConst &pc, hipStream_t s) {
     const int bytes = resident_lds(nmax);
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_resident<PREC, GEN, S>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+    hipError_t e = allow_lds(k_resident<PREC, GEN, S>, bytes, resident_lds(kResidentMax));
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((k_resident<PREC, GEN, S>), dim3(nclusters), dim3((nmax * S + 63) / 64 * 64), bytes, s, o, pc);
     return hipGetLastError();

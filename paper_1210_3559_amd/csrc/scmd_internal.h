@@ -44,6 +44,16 @@ struct PotConst {
     int generic;      // 1 unless (n, m) == (9, 6)
 };
 
+// Allows the kernel more dynamic LDS than the default 64 KiB before a launch that
+// needs it.  The limit belongs to the kernel and is shared by every context and
+// thread: all of a kernel's launches set the same one, the `most` that any needs.
+template <typename K>
+inline hipError_t allow_lds(K kernel, size_t bytes, size_t most) {
+    if (bytes <= 65536) return hipSuccess;
+    return hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                               (int)most);
+}
+
 // One cluster of a batch (device table).
 struct ClusterDesc {
     int32_t off;        // first atom
@@ -295,6 +305,7 @@ hipError_t launch_fetch_samples(const double *ring, int cap, int nclusters, int 
 // cluster: step, E_pot, E_kin, T, T_target).
 hipError_t launch_sample(const ClusterState *st, int nclusters, double *ring, int slot, int64_t step, hipStream_t s);
 
+constexpr int kRdfMaxBins = 32768;  // LDS histogram of 128 KiB
 // Pair-distance histogram of the atoms [off, off + n) (analysis.hip): refs
 // (n entries) and nref receive the reference atoms; counts (nbins) is
 // cleared first when `clear`, then the pairs are added to it; nref_total,

@@ -234,7 +234,6 @@ int fail(scmd_ctx *c, int code, const std::string &msg) {
 constexpr int kRowSingleMax = 3072;
 constexpr double kRowBatchPairs = 2.5e7, kRowBatchPairsLarge = 2.5e6;
 constexpr int kRowBatchSmall = 384;
-constexpr int kRdfMaxBins = 32768;  // LDS histogram of 128 KiB
 
 int64_t ndof_of(int64_t n) {
     if (n >= 3) return 3 * n - 6;

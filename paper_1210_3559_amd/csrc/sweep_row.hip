@@ -422,33 +422,25 @@ __global__ __launch_bounds__(64 * W) void k_row_force(RowArgs ra, const double4 
     }
 }
 
-// Allow the kernel the dynamic LDS it needs (above the 64 KiB default).
-template <typename K>
-hipError_t allow_lds(K kernel, size_t bytes) {
-    if (bytes <= 65536) return hipSuccess;
-    return hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                               (int)bytes);
-}
-
 template <int W, int PREC, bool GEN, bool STAGE>
 hipError_t row_launch(bool force, bool energy, const RowLaunch &L, const SweepBuffers &B, const ForceOut &fo,
                       const DriftArgs &da, const PotConst &pc, hipStream_t s) {
     const RowArgs ra{L.tiles, L.order, L.cd, L.uni_off, L.uni_n, L.uni_ni};
     hipError_t e;
     if (force) {
-        const size_t lds = row_lds_bytes<W, 4, STAGE>(L.nmax);
+        const size_t lds = row_lds_bytes<W, 4, STAGE>(L.nmax), most = row_lds_bytes<W, 4, STAGE>(kRowStageMax);
         // the bath epilogue exists only in fused (staged) launches
         constexpr bool kB = STAGE;
         auto kern = energy ? (fo.bath ? k_row_force<W, PREC, GEN, STAGE, true, kB>
                                       : k_row_force<W, PREC, GEN, STAGE, true, false>)
                            : (fo.bath ? k_row_force<W, PREC, GEN, STAGE, false, kB>
                                       : k_row_force<W, PREC, GEN, STAGE, false, false>);
-        if ((e = allow_lds(kern, lds)) != hipSuccess) return e;
+        if ((e = allow_lds(kern, lds, most)) != hipSuccess) return e;
         hipLaunchKernelGGL(kern, dim3(L.ntiles), dim3(64 * W), lds, s, ra, (const double4 *)B.xp, fo, pc);
     } else {
-        const size_t lds = row_lds_bytes<W, 1, STAGE>(L.nmax);
+        const size_t lds = row_lds_bytes<W, 1, STAGE>(L.nmax), most = row_lds_bytes<W, 1, STAGE>(kRowStageMax);
         auto kern = k_row_density<W, PREC, GEN, STAGE>;
-        if ((e = allow_lds(kern, lds)) != hipSuccess) return e;
+        if ((e = allow_lds(kern, lds, most)) != hipSuccess) return e;
         const DensityOut dout{B.rp, B.xp, B.rho, B.tile_sums};
         hipLaunchKernelGGL(kern, dim3(L.ntiles), dim3(64 * W), lds, s, ra, dout, pc, da);
     }

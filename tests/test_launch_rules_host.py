@@ -65,3 +65,29 @@ for n in (700, 2560, 2561, 4096):
             result.append([n, tuning.get("waves_j", 0), sorted({r[3] // 64 for r in records() if r[0] == "launch" and "k_row" in r[1]})])
 """)
     assert all(waves == [asked or 8] for _, asked, waves in got), got
+
+
+def test_the_lds_limit_of_a_kernel_does_not_depend_on_the_call():
+    # the limit belongs to the kernel: a smaller one, set by a context on another
+    # thread, must not come between a context's own setting and its launch
+    got = recorder.run("""
+result = []
+for n in (13, 48, 49, 96, 97, 152, 700, 2243, 2500, 2600, 3000):
+    for kw in ({}, dict(precision="mixed"), dict(params=dict(n=12, m=6)), dict(rc=8.8)):
+        with scmd.Simulation([0, n], cluster(n), **kw) as sim:
+            sim.step(2)
+            for bins in (100, 20000, 32768):
+                sim.rdf(0, 0.01, bins)
+        result += records()
+""")
+    limits, lds = {}, {}
+    for kind, kernel, *nums in got:
+        if kind == "limit":
+            limits.setdefault(kernel, set()).add(nums[0])
+        else:
+            lds[kernel] = max(lds.get(kernel, 0), nums[2])
+    for family in ("k_resident", "k_row_density", "k_row_force", "k_rdf_hist", "k_cell_sweep"):
+        assert any(family in k for k in limits), family
+    for kernel, bytes_ in lds.items():
+        assert len(limits.get(kernel, {65536})) == 1, kernel
+        assert bytes_ <= min(limits.get(kernel, {65536})), kernel
