@@ -18,8 +18,8 @@ constexpr double kBoltzmannEv = 8.617333262145179e-05;
 // single precision), and no sentinel ever meets another at r = 0.
 constexpr double kFar = 1.0e150;
 // The same where up to four pairs share one reciprocal of their r^2 (density of
-// the symmetric sweeps): r^2 ~ 1e76, so the product of four stays finite; u^6 is
-// 1e-228, lost beside any real term and cleared where there is none.
+// the symmetric sweeps): r^2 ~ 1e76, so the product of four stays finite; u^6 is at
+// most 5e-227, lost beside any real term and cleared where there is none.
 constexpr double kFarShared = 3.0e37;
 
 // Sutton-Chen constants folded for the kernels.  With u = 1/r:

@@ -302,6 +302,9 @@ __device__ __forceinline__ double density_term(double r2, const PotConst &pc) {
 // one reciprocal per pair / shared: 48,077 atoms 1415 / 1386, 256 clusters 968 /
 // 953, 15,000 atoms 172.2 / 167.9, 3001 atoms 23.7 / 23.2; density error against
 // 80-bit sums (rms over nine sizes) 3.7e-16 / 2.6e-16.
+// A product that leaves the range (a pair at r = 0, four beyond ~1e38 A) makes all
+// its terms NaN: sums that are not finite are taken again pair by pair when an atom
+// is finished.
 template <int PREC, int N>
 __device__ __forceinline__ void density_terms(const double (&r2)[N], double (&t)[N], const PotConst &pc) {
     static_assert(N == 2 || N == 4, "pairs or pairs of pairs");

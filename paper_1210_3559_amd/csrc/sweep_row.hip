@@ -321,6 +321,13 @@ __global__ __launch_bounds__(64 * W) void k_row_density(RowArgs ra, DensityOut o
         qi = src[i_local];
         row_loop(L, src, rt.n, i_local, pair, quad, 0, L.k_end);
     }
+    if constexpr (PREC == SCMD_FP64 && !GEN) {
+        // a product of four r^2 left the range (density_terms): pair by pair
+        if (!isfinite(acc)) {
+            acc = 0.0;
+            for (int j = L.s; j < rt.n; j += L.S) pair(src[j], j == i_local);
+        }
+    }
     double v[1] = {acc};
     row_reduce<W, 1>(L, v, sh);
     double emb = 0.0;

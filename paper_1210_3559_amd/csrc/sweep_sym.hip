@@ -502,32 +502,42 @@ __device__ __forceinline__ void sym_sums(const SymTile &t, const double *__restr
     __syncthreads();
 }
 
+// shared: the sweep's pairs shared reciprocals (double).  A product of r^2 that
+// left the range then made all its terms NaN: a sum that is not finite is taken
+// again here, pair by pair, so that only pairs bad by themselves spoil it.  (Voting
+// on it and repeating the item inside the sweep cost 0.3 to 0.9 % of a step.)
 template <int IPT>
 __global__ __launch_bounds__(kSymRed) void k_sym_density_reduce(const SymTile *__restrict__ tiles,
                                                                 const double *__restrict__ ipart,
                                                                 const double *__restrict__ jpart, DensityOut o,
-                                                                PotConst pc, DriftArgs da) {
+                                                                PotConst pc, DriftArgs da, bool shared) {
     __shared__ double sh[kSymRedGroups * 64];
     const SymTile t = tiles[blockIdx.x];
-    // the atom's position, as the sweep had it, is fetched ahead of the sums
+    const bool bath = da.mode != 0 && in_bath(t.c, da);
+    const double lam = da.mode != 0 ? da.st[t.c].lambda : 1.0;
+    // an atom's position, as the sweep had it
+    auto position = [&](int i) { return da.mode != 0 ? drifted_atom(o.rp, i, da, bath, lam) : o.rp[i]; };
+    // fetched ahead of the sums
     double4 q = make_double4(0, 0, 0, 0);
-    if (threadIdx.x < t.ni) {
-        const int i = t.i0 + threadIdx.x;
-        if (da.mode != 0) {
-            const bool bath = in_bath(t.c, da);
-            q = drifted_atom(o.rp, i, da, bath, da.st[t.c].lambda);
-        } else {
-            q = o.rp[i];
-        }
-    }
+    if (threadIdx.x < t.ni) q = position(t.i0 + threadIdx.x);
     sym_sums<IPT, 1, false>(t, ipart, jpart, sh);
     if (threadIdx.x >= 64) return;
     double emb = 0.0;
     if (threadIdx.x < t.ni) {
-        // sums of sentinels alone (~1e-228 each; a pair 1e12 A apart gives
-        // 1e-72): the atom has no neighbour
-        const double u6 = sh[threadIdx.x];
-        emb = density_atom_at(t.i0 + threadIdx.x, u6 < 1.0e-180 ? 0.0 : u6, q, o, pc);
+        double u6 = sh[threadIdx.x];
+        if (shared && !isfinite(u6)) {
+            const int i = t.i0 + threadIdx.x, a = da.cd[t.c].off, b = a + da.cd[t.c].n;
+            u6 = 0.0;
+            for (int j = a; j < b; ++j) {
+                const double4 p = position(j);
+                const double dx = q.x - p.x, dy = q.y - p.y, dz = q.z - p.z;
+                if (j != i)
+                    u6 += density_term<SCMD_FP64, false>(__builtin_fma(dx, dx, __builtin_fma(dy, dy, dz * dz)), pc);
+            }
+        }
+        // sums of sentinels alone (5e-227 each, a few hundred at most; a pair 1e12
+        // A apart gives 1e-72): the atom has no neighbour
+        emb = density_atom_at(t.i0 + threadIdx.x, u6 < 1.0e-220 ? 0.0 : u6, q, o, pc);
     }
     emb = wave_total(emb);
     if (threadIdx.x == 0) o.tile_sums[(size_t)blockIdx.x * kTileSums + 0] = emb;
@@ -595,7 +605,7 @@ hipError_t launch_ipt(bool force, int stage, bool energy, const SymLaunch &L, co
         } else {
             const DensityOut o{B.rp, B.xp, B.rho, B.tile_sums};
             hipLaunchKernelGGL((k_sym_density_reduce<IPT>), dim3(L.ntiles), dim3(kSymRed), 0, s, L.tiles, L.ipart,
-                               L.jpart, o, pc, da);
+                               L.jpart, o, pc, da, PREC == SCMD_FP64);
         }
     }
     return hipGetLastError();
