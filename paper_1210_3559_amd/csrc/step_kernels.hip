@@ -81,8 +81,9 @@ __global__ __launch_bounds__(256) void k_bath_prep(const int32_t *__restrict__ a
 // every workgroup finds the thermostat factor itself from the cluster's v^2
 // sums (same order as the finalize, so the same bits everywhere), which saves a
 // launch per step; without a rescaling thermostat the factor is 1 and no sum is
-// read.  Energies are nobody's business until the run's last step.  CELL: the
-// cell list's check on the drifted positions as well (another launch saved).
+// read.  Energies are nobody's business until the run's last step (of them only a
+// rescaled kinetic energy can be non-finite before it and finite again there).
+// CELL: the cell list's check on the drifted positions as well (another launch saved).
 template <bool CELL>
 __global__ __launch_bounds__(256) void k_drift_fin(dev::FinalizeArgs fa, double4 *__restrict__ rp,
                                                    double4 *__restrict__ v, const double4 *__restrict__ f,
@@ -94,8 +95,10 @@ __global__ __launch_bounds__(256) void k_drift_fin(dev::FinalizeArgs fa, double4
     if (d0.kind == SCMD_BERENDSEN) {
         double e0, e1, v2, tt;
         dev::cluster_totals<true>(d0, fa.tile_sums, sh, e0, e1, v2);
-        lam = dev::thermostat_lambda(d0, fa.dt, dev::kinetic_temperature(d0, fa.mass_u, v2).T,
-                                     fa.st[0].step + fa.step_add, &tt);
+        const dev::KinT kt = dev::kinetic_temperature(d0, fa.mass_u, v2);
+        lam = dev::thermostat_lambda(d0, fa.dt, kt.T, fa.st[0].step + fa.step_add, &tt);
+        // the factor may hide an overflow from the run's last step
+        if (blockIdx.x == 0 && threadIdx.x == 0 && !isfinite(kt.ke)) dev::raise_flag(fa.flag);
     }
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     dev::CellBox b;

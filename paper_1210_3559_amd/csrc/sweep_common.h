@@ -701,6 +701,7 @@ struct DriftArgs {
     const double *tile_sums;
     const ClusterDesc *cd;
     double mass_u, dt, h, dth;
+    int *flag;  // non-finite flag
 };
 
 // Drifted position p + (dt lambda) v with p = r + (dt h) F (Drift).
@@ -740,8 +741,11 @@ __device__ __forceinline__ bool in_bath(int c, const DriftArgs &da) {
 // the previous step's factor, finished here from the cluster's v^2 tile sums in
 // the finalize's order, and stored by the one workgroup with `writer`).  A
 // cluster in a Langevin bath has its drifted (r, v) stored already: factor 0
-// (the row sweeps take p + 0 v = p).  Whole workgroups of >= 256 threads; sh
-// needs 12 doubles.
+// (the row sweeps take p + 0 v = p).  REPORT: the writer reports a kinetic energy
+// that is not finite, which the factor may hide from the run's last step (the row
+// sweeps and resident runs look at their last step only).  Whole workgroups of
+// >= 256 threads; sh needs 12 doubles.
+template <bool REPORT>
 __device__ __forceinline__ double drift_factor(int c, const DriftArgs &da, bool bath, double *sh, bool writer) {
     if (bath) return 0.0;
     ClusterState *sc = da.st + c;
@@ -752,7 +756,10 @@ __device__ __forceinline__ double drift_factor(int c, const DriftArgs &da, bool 
     const KinT kt = kinetic_temperature(d, da.mass_u, v2);
     double tt;
     const double lam = thermostat_lambda(d, da.dt, kt.T, sc->step + da.local, &tt);
-    if (writer && threadIdx.x == 0) sc->lambda = lam;
+    if (writer && threadIdx.x == 0) {
+        sc->lambda = lam;
+        if (REPORT && !isfinite(kt.ke)) raise_flag(da.flag);
+    }
     return lam;
 }
 
@@ -871,8 +878,8 @@ __device__ __forceinline__ FusedAtom fused_atom_load(int i, int c, bool bath, co
 
 // Host: the arguments of the folded drift and of the force epilogues.
 inline DriftArgs drift_args(const SweepBuffers &B, const StepArgs &a, const Drift &dr) {
-    return DriftArgs{dr.mode, dr.local, dr.bath, B.v, B.f, B.dpv, a.st, B.tile_sums, a.cd, a.mass_u, a.dt, a.h,
-                     a.dt * a.h};
+    return DriftArgs{dr.mode, dr.local, dr.bath, B.v, B.f,  B.dpv,      a.st,
+                     B.tile_sums, a.cd, a.mass_u, a.dt, a.h, a.dt * a.h, a.flag};
 }
 // (the fused epilogue stores the drifted positions: rp is the context's
 // writable position array, which the sweeps otherwise only read)

@@ -295,7 +295,7 @@ __global__ __launch_bounds__(64 * W) void k_row_density(RowArgs ra, DensityOut o
             if (a2 < rt.n) t2 = load(a2);
             if (a3 < rt.n) t3 = load(a3);
             __shared__ double sh_tot[12];
-            const double dtl = da.dt * drift_factor(rt.c, da, bath, sh_tot, rt.first);
+            const double dtl = da.dt * drift_factor<false>(rt.c, da, bath, sh_tot, rt.first);
             qi = drifted(own, dtl);
             if (a0 < rt.n) lj[a0] = drifted(t0, dtl);
             if (a1 < rt.n) lj[a1] = drifted(t1, dtl);

@@ -327,7 +327,7 @@ __global__ __launch_bounds__(64 * NW) void k_sym_density(const SymItem *__restri
         if (da.mode != 0) {
             __shared__ double sh_tot[12];
             bath = in_bath(it.c, da);
-            lam = drift_factor(it.c, da, bath, sh_tot, it.first != 0);
+            lam = drift_factor<true>(it.c, da, bath, sh_tot, it.first != 0);
         }
     }
     auto position = [&](int i) {
