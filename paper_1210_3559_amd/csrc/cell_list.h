@@ -22,14 +22,15 @@ hipError_t cell_list_plan(CellList *cl, int nclusters, const int64_t *offsets, d
                           const double4 *rp);
 // The force sweep stores each cell's energy and v^2 sums (kTileSums doubles)
 // at the cell's index: cluster c owns slots [first, first + count) of
-// total_slots, and the per-cluster finish adds those.
+// total_slots, and the per-cluster finish adds those.  A build zeroes the slots of
+// empty cells that the sweeps do not visit.
 void cell_list_sum_slots(const CellList *cl, int cluster, int *first, int *count);
 int cell_list_total_slots(const CellList *cl);
 // Displacement check, then the rebuild of the cells when it is due (the
 // density sweep of the same evaluation rebuilds the lists).  checked: the
 // kernel that drifted the atoms already ran the check (cell_list_check) on
-// these positions.
-hipError_t cell_list_build(CellList *cl, const double4 *rp, bool checked, hipStream_t s);
+// these positions.  sums: the slots (B.tile_sums of the sweeps).
+hipError_t cell_list_build(CellList *cl, const double4 *rp, double *sums, bool checked, hipStream_t s);
 // The check's arguments, for the drift kernel of a single cluster to run it.
 CellCheck cell_list_check(CellList *cl);
 // Rebuilds of the cells and lists since the plan (synchronous read).
@@ -41,8 +42,8 @@ hipError_t cell_list_invalidate(CellList *cl, hipStream_t s);
 // the natoms-entry device buffer scratch_dev) exactly as that build made
 // them, so that a resumed run continues bit for bit.
 hipError_t cell_list_get_ref(CellList *cl, double4 *host_out);
-hipError_t cell_list_restore(CellList *cl, const double4 *ref_host, double4 *scratch_dev, const PotConst &pc,
-                             int precision, hipStream_t s);
+hipError_t cell_list_restore(CellList *cl, const double4 *ref_host, double4 *scratch_dev, double *sums,
+                             const PotConst &pc, int precision, hipStream_t s);
 // Density and force sweeps over the cell list; each finishes its atoms with
 // the same per-atom epilogues as the all-pairs reduce kernels (density: rho,
 // P into xp; force: F, the kick when a.advance), and the force sweep stores

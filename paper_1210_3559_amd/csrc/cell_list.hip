@@ -22,7 +22,8 @@
 //           resets the boxes for the next check;
 //   order   per cell: its work record; every atom's slot becomes its rank by
 //           atom index, so the cell-sorted order is deterministic; positions
-//           are gathered; the counts are cleared for the next build.
+//           are gathered; the counts are cleared for the next build, and the
+//           sums of cells that the sweeps will not come to.
 // Sweeps: one workgroup per cell (fullest cells first); the candidates of
 // the 27 neighbouring cells (9 contiguous x-rows of the sorted arrays) are
 // staged in LDS, and each wavefront takes the cell's atoms one at a time
@@ -50,9 +51,10 @@ struct CellGrid {
     int pad;
 };
 
-// What a sweep's workgroup needs to know of its cell, made by the build for
-// every place in the sweeps' order: one uniform load instead of a chain of five
-// (order, cluster, grid, starts) ahead of the staging.
+// What a sweep's workgroup needs to know of its cell, made by the build for the
+// places in the sweeps' order that can hold atoms (the fullest cells come first, so
+// the first natoms): one uniform load instead of a chain of five (order, cluster,
+// grid, starts) ahead of the staging.
 struct CellWork {
     int cell, s0, cnt;  // cell, its first sorted atom, its atoms (0: nothing to do)
     int m;              // candidates: atoms of the 27 cells
@@ -78,7 +80,8 @@ struct CellList {
     int *start = nullptr;         // [total_cap + 1]
     int *cursor = nullptr;        // [total_cap]
     int *corder = nullptr;        // [total_cap] cells in the order the sweeps take them (fullest first)
-    CellWork *work = nullptr;     // [total_cap] the same order
+    int nwork = 0;                // places that can hold atoms, at least one
+    CellWork *work = nullptr;     // [nwork] the same order
     int *cell_of = nullptr;       // [natoms]
     int *perm = nullptr;          // cell slot -> atom, as scattered
     int *sperm = nullptr;         // cell slot -> atom, sorted by atom index within each cell
@@ -399,12 +402,17 @@ __global__ __launch_bounds__(64) void k_cell_order(const int *__restrict__ start
                                                    int *__restrict__ slot_of, const CellGrid *__restrict__ grid,
                                                    const int *__restrict__ cell_cluster,
                                                    const int *__restrict__ corder, CellWork *__restrict__ work,
+                                                   int nwork, double *__restrict__ sums,
                                                    int *__restrict__ count, int *__restrict__ cursor,
                                                    const int *__restrict__ flag) {
     __shared__ int sh[kOrderLds];
     if (*flag == 0) return;
     const int cell = corder[blockIdx.x];
     if (threadIdx.x == 0) count[cell] = cursor[cell] = 0;  // for the next build
+    if ((int)blockIdx.x >= nwork) {  // an empty cell; the sweeps end before it
+        if (threadIdx.x < 3) sums[(size_t)cell * kTileSums + threadIdx.x] = 0.0;
+        return;
+    }
     const CellGrid g = grid[cell_cluster[cell]];
     const int local_cell = cell - g.base;
     const int a = start[cell];
@@ -511,8 +519,7 @@ __global__ __launch_bounds__(64 * kCellWaves, 8) void k_cell_sweep(const CellWor
     if (FORCE && blockIdx.x == 0 && threadIdx.x == 0) *flag = 0;
     const int s0 = w.s0, cnt = w.cnt;
     // the cell's slot of the cluster sums (embedding energy, pair energy,
-    // v^2), stored by the force sweep; cells without atoms, also those
-    // beyond this build's grid, hold zeros
+    // v^2), stored by the force sweep; cells without atoms hold zeros
     if (cnt == 0) {  // uniform per workgroup
         if (FORCE && finish && threadIdx.x == 0) {
             double *const cell_sums = fout.tile_sums + (size_t)w.cell * kTileSums;
@@ -738,7 +745,7 @@ template <bool FORCE>
 hipError_t launch_cell_sweep(CellList *cl, const double4 *xp, const DensityOut &dout, const ForceOut &fout,
                              int finish, const PotConst &pc, int precision, hipStream_t s) {
     (void)hipGetLastError();
-    const dim3 grid(cl->total_cap), block(64 * kCellWaves);
+    const dim3 grid(cl->nwork), block(64 * kCellWaves);
     const size_t lds = kCellStage * sizeof(double4);
 #define SCMD_CELL_ARGS                                                                                          \
     cl->work, cl->rs, cl->sperm, cl->fin, cl->emb, cl->nbr, cl->nbr_n, xp, pc, cl->flag, cl->rl * cl->rl, dout, fout, \
@@ -868,7 +875,8 @@ hipError_t cell_list_plan(CellList *cl, int nclusters, const int64_t *offsets, d
     if ((e = dalloc(&cl->start, base + 1)) != hipSuccess) return e;
     if ((e = dalloc(&cl->cursor, base)) != hipSuccess) return e;
     if ((e = dalloc(&cl->corder, base)) != hipSuccess) return e;
-    if ((e = dalloc(&cl->work, base)) != hipSuccess) return e;
+    cl->nwork = std::max(1, std::min(base, natoms));
+    if ((e = dalloc(&cl->work, cl->nwork)) != hipSuccess) return e;
     if ((e = dalloc(&cl->cell_of, natoms)) != hipSuccess) return e;
     if ((e = dalloc(&cl->perm, natoms)) != hipSuccess) return e;
     if ((e = dalloc(&cl->sperm, natoms)) != hipSuccess) return e;
@@ -932,7 +940,7 @@ CellCheck cell_list_check(CellList *cl) {
     return CellCheck{cl->ref, cl->slot_of, cl->rs, cl->box, cl->flag, check_thr2(cl)};
 }
 
-hipError_t cell_list_build(CellList *cl, const double4 *rp, bool checked, hipStream_t s) {
+hipError_t cell_list_build(CellList *cl, const double4 *rp, double *sums, bool checked, hipStream_t s) {
     (void)hipGetLastError();
     const int na = cl->natoms, tc = cl->total_cap;
     const double thr2 = check_thr2(cl);
@@ -958,8 +966,8 @@ hipError_t cell_list_build(CellList *cl, const double4 *rp, bool checked, hipStr
     // count and scatter read the previous build's order from sperm before
     // k_cell_order replaces it
     hipLaunchKernelGGL(k_cell_order, dim3(tc), dim3(64), 0, s, cl->start, cl->perm, cl->sperm, rp, cl->rs, cl->ref,
-                       cl->slot_of, cl->grid, cl->cell_cluster, cl->corder, cl->work, cl->count, cl->cursor,
-                       cl->flag);
+                       cl->slot_of, cl->grid, cl->cell_cluster, cl->corder, cl->work, cl->nwork, sums, cl->count,
+                       cl->cursor, cl->flag);
     return hipGetLastError();
 }
 
@@ -983,8 +991,8 @@ hipError_t cell_list_get_ref(CellList *cl, double4 *host_out) {
     return hipMemcpy(host_out, cl->ref, cl->natoms * sizeof(double4), hipMemcpyDeviceToHost);
 }
 
-hipError_t cell_list_restore(CellList *cl, const double4 *ref_host, double4 *scratch_dev, const PotConst &pc,
-                             int precision, hipStream_t s) {
+hipError_t cell_list_restore(CellList *cl, const double4 *ref_host, double4 *scratch_dev, double *sums,
+                             const PotConst &pc, int precision, hipStream_t s) {
     if (cl->natoms == 0) return cell_list_invalidate(cl, s);
     hipError_t e = hipMemcpyAsync(scratch_dev, ref_host, cl->natoms * sizeof(double4), hipMemcpyHostToDevice, s);
     if (e != hipSuccess) return e;
@@ -992,7 +1000,7 @@ hipError_t cell_list_restore(CellList *cl, const double4 *ref_host, double4 *scr
     // them: a build forced from those positions, then a density sweep that
     // lists the candidates and finishes no atom
     if ((e = cell_list_invalidate(cl, s)) != hipSuccess) return e;
-    if ((e = cell_list_build(cl, scratch_dev, false, s)) != hipSuccess) return e;
+    if ((e = cell_list_build(cl, scratch_dev, sums, false, s)) != hipSuccess) return e;
     if ((e = launch_cell_sweep<false>(cl, nullptr, DensityOut{}, ForceOut{}, 0, pc, precision, s)) != hipSuccess)
         return e;
     // the density sweep left the flag set: clear it (the lists hold)

@@ -848,7 +848,7 @@ hipError_t enqueue_sweeps(scmd_ctx *c, hipStream_t s, bool capturing, int advanc
         return c->sym ? launch_sym_force(L, B, A, fused, local, bath, c->pc, c->precision, 1, s) : hipSuccess;
     }
     if (c->neighbour == SCMD_CELLLIST) {
-        if ((e = cell_list_build(c->cells, c->rp.p, checked, s)) != hipSuccess) return e;
+        if ((e = cell_list_build(c->cells, c->rp.p, c->d_tile_sums.p, checked, s)) != hipSuccess) return e;
     }
     if ((e = sweep(c, false, s, capturing, advance)) != hipSuccess) return e;
     if (c->has_split && (e = launch_density_reduce(c->d_tiles.p, c->ntiles, c->tile, B, c->pc, 2, s)) != hipSuccess)
@@ -1909,8 +1909,8 @@ int scmd_set_state(scmd_ctx *ctx, const void *buf, size_t bytes) {
             for (size_t k = 0; k < 4 * (size_t)ctx->natoms && !have_ref; ++k) have_ref = ((const double *)p)[k] != 0.0;
             if (have_ref) {
                 HIP_TRY(ctx, ctx->restore_scratch.ensure(std::max(ctx->natoms, 1)));
-                HIP_TRY(ctx, cell_list_restore(ctx->cells, (const double4 *)p, ctx->restore_scratch.p, ctx->pc,
-                                               ctx->precision, ctx->stream));
+                HIP_TRY(ctx, cell_list_restore(ctx->cells, (const double4 *)p, ctx->restore_scratch.p,
+                                               ctx->d_tile_sums.p, ctx->pc, ctx->precision, ctx->stream));
             } else {
                 HIP_TRY(ctx, cell_list_invalidate(ctx->cells, ctx->stream));
             }

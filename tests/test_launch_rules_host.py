@@ -91,3 +91,20 @@ for n in (13, 48, 49, 96, 97, 152, 700, 2243, 2500, 2600, 3000):
     for kernel, bytes_ in lds.items():
         assert len(limits.get(kernel, {65536})) == 1, kernel
         assert bytes_ <= min(limits.get(kernel, {65536})), kernel
+
+
+def test_cell_list_memory_of_a_sparse_box():
+    # two atoms 1000 A apart span about 1.6 million cells; a cell needs its
+    # cluster, count, start, cursor and place (4 bytes each) and a slot of 32
+    # bytes for its sums, records are for cells that can hold atoms
+    got = recorder.run("""
+pos = np.array([[0.0, 0.0, 0.0], [1000.0, 1000.0, 1000.0]])
+with scmd.Simulation([0, 2], pos, rc=8.8) as sim:
+    before = rec.rec_device_bytes()
+    sim.compute()
+    cells = max(r[2] for r in records() if "k_cell_order" in r[1])
+    result = [cells, rec.rec_device_bytes() - before]
+""")
+    cells, added = got
+    assert cells > 10**6
+    assert added <= 52 * cells + 65536, added / cells
