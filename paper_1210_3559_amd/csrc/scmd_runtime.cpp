@@ -596,10 +596,15 @@ int build_plan(scmd_ctx *c, std::vector<ITile> *tiles_out) {
             // group mean fewer moves per pair but fewer, longer items; us per
             // step at (2 tiles, 1024 items) / (4, 2048) / (8, 8192): 6001
             // atoms 46.5 / 55.9, 9000: 81.1 / 80.4, 15000: 188 / 170,
-            // 32000: 749 / 678, 48077: - / 1484 / 1408; below 4200 atoms 512
-            // items beat 1024 (4097: 31.0 / 34.6).
+            // 32000: 749 / 678, 48077: - / 1484 / 1408.  From 56 to 65 tiles
+            // 1024 means one j tile per item and more than the 768 items that
+            // three per CU take at once; two j tiles per item (512) are faster
+            // there: 3501 atoms (55 tiles) 28.0 at 1024 / 28.8 at 512, 3584 (56)
+            // 30.5 / 28.8, 4032: 31.6 / 30.4, 4160 (65): 34.1 / 30.8, 4224 (66,
+            // two j tiles at 1024 as well) 34.4 / 35.3.
+            const int64_t tiles = (nmax + 63) / 64;
             int ipt = nmax > 32768 ? 8 : nmax > 9000 ? 4 : 2;
-            int target = nmax > 32768 ? 8192 : nmax > 9000 ? 2048 : nmax > 3600 && nmax <= 4200 ? 512 : 1024;
+            int target = nmax > 32768 ? 8192 : nmax > 9000 ? 2048 : tiles >= 56 && tiles <= 65 ? 512 : 1024;
             if (batch) {
                 // 4 x 2057 (8.5e6 pairs) 30.7 us at 512 items, 33.7 at 1024;
                 // 15 x 2057 (3.2e7) 70.7 at 1024, 68.8 at 2048; 40 clusters

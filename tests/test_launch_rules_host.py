@@ -108,3 +108,16 @@ with scmd.Simulation([0, 2], pos, rc=8.8) as sim:
     cells, added = got
     assert cells > 10**6
     assert added <= 52 * cells + 65536, added / cells
+
+
+def test_symmetric_items_of_middle_sizes_fit_three_per_compute_unit():
+    # one j tile per item while that is at most 768 items, then two (1024 items
+    # asked for give two from 66 tiles on)
+    got = recorder.run("""
+result = []
+for n in (3073, 3520, 3521, 3600, 4096, 4160, 4161, 4480):
+    with scmd.Simulation([0, n], cluster(n)) as sim:
+        sim.compute()
+        result.append([n, max(r[2] for r in records() if r[0] == "launch" and "k_sym_force" in r[1])])
+""")
+    assert all(items <= 768 for _, items in got), got
