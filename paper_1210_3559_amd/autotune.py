@@ -1,12 +1,15 @@
 """Launch-shape autotuner for the all-pairs sweeps and the cell list.
 
-For an all-pairs workload it times every supported (ipt, waves_i, waves_j)
-shape and a few work-splitting targets with whole velocity-Verlet steps
-replayed from HIP graphs, and keeps the fastest; for a cell-list workload it
+For an all-pairs workload it times the library's own plan, every supported
+(ipt, waves_i, waves_j) shape and a few work-splitting targets with whole
+velocity-Verlet steps, and keeps the fastest (the library's own plan only where
+it is clearly faster: it may change with the library); for a cell-list workload it
 times the list skin (``cell_skin``: a longer list against fewer rebuilds).
 Results are cached as JSON keyed by (device architecture, precision,
 cluster-size bucket, cluster count bucket, and "cell" for the cell list), so
-``Simulation(..., tuning="auto")`` can pick them up later.
+``Simulation(..., tuning="auto")`` can pick them up later.  A launch plan is
+looked up only for clusters within an eighth of the size it was timed at: a
+bucket spans a factor of two, over which the best plan changes.
 
     python -m paper_1210_3559_amd.autotune --workloads ni2243_cooling,batch256 [--cache PATH]
 """
@@ -32,11 +35,18 @@ CELL_SKINS = [0.2, 0.3, 0.4, 0.5, 0.6]  # A; rebuilds every step at 0, LDS stage
 # measured on MI355X by `python -m paper_1210_3559_amd.autotune` and committed with the package
 DEFAULT_CACHE = os.path.join(os.path.dirname(os.path.abspath(__file__)), "tuning_cache.json")
 ARCH = "gfx950"
+DEFAULT_GAIN = 0.97  # the library's own plan is kept below this share of the best other plan's time
+SIZE_RANGE = 1.125  # a plan timed at nmax atoms holds for [nmax / SIZE_RANGE, nmax * SIZE_RANGE]
+
+
+def _nmax(offsets) -> int:
+    sizes = np.diff(np.asarray(offsets))
+    return int(sizes.max()) if len(sizes) else 0
 
 
 def bucket(offsets, precision: str, cell: bool = False) -> str:
     sizes = np.diff(np.asarray(offsets))
-    nmax = int(sizes.max()) if len(sizes) else 0
+    nmax = _nmax(offsets)
     key = f"{ARCH}/{precision}/nmax2^{max(0, math.ceil(math.log2(max(nmax, 1))))}/nc2^{math.ceil(math.log2(max(len(sizes), 1)))}"
     return key + "/cell" if cell else key
 
@@ -49,17 +59,12 @@ def _time(sim: "scmd.Simulation", steps: int) -> float:
 
 def tune(w, precision: str | None = None, budget_s: float = 0.25, shapes=SHAPES, targets=TARGETS, verbose=True,
          symmetric: bool = True, row: bool = True):
-    """Time every shape/target (cell list: every skin) on workload w; returns
-    (best tuning dict, table)."""
+    """Time every plan of `tunings` on workload w; returns (best tuning dict,
+    table)."""
     precision = precision or w.precision
     pairs = float(np.sum(w.sizes().astype(np.float64) ** 2))
     table = []
-    if w.rc > 0:
-        tunings = [dict(cell_skin=s) for s in CELL_SKINS]
-    else:
-        tunings = [dict(cand, target_items=tgt) for cand, tgts in candidate_plans(w.sizes(), shapes, targets,
-                                                                                  symmetric, row) for tgt in tgts]
-    for tun in tunings:
+    for tun in tunings(w, shapes, targets, symmetric, row):
         with scmd.Simulation.from_workload(w, precision=precision, tuning=tun) as sim:
             sim.step(32)
             dt1 = _time(sim, 32)
@@ -71,8 +76,24 @@ def tune(w, precision: str | None = None, budget_s: float = 0.25, shapes=SHAPES,
             rate = (f"{w.n_atoms / dt:.4g} atom-steps/s" if w.rc > 0 else
                     f"{pairs / dt / 1e9:.1f} G ordered pairs/s")
             print(f"[tune] {w.name} {precision} {tun} {1e3 * dt:.4f} ms/step ({rate})", file=sys.stderr, flush=True)
-    best = min(table, key=lambda r: r["ms_per_step"])
-    return best["tuning"], table
+    return pick(table)["tuning"], table
+
+
+def tunings(w, shapes=SHAPES, targets=TARGETS, symmetric: bool = True, row: bool = True):
+    """What is timed for workload w: the library's own plan ({}) and every
+    shape/target, or every skin of the cell list."""
+    if w.rc > 0:
+        return [dict(cell_skin=s) for s in CELL_SKINS]
+    return [{}] + [dict(cand, target_items=tgt)
+                   for cand, tgts in candidate_plans(w.sizes(), shapes, targets, symmetric, row) for tgt in tgts]
+
+
+def pick(table):
+    """The fastest row of a timing table; the library's own plan only if it is
+    clearly faster than every other."""
+    other = min((r for r in table if r["tuning"]), key=lambda r: r["ms_per_step"])
+    own = [r for r in table if not r["tuning"]]
+    return own[0] if own and own[0]["ms_per_step"] < DEFAULT_GAIN * other["ms_per_step"] else other
 
 
 def candidate_plans(sizes, shapes=SHAPES, targets=TARGETS, symmetric: bool = True, row: bool = True):
@@ -104,9 +125,15 @@ def load_cache(path: str = DEFAULT_CACHE) -> dict:
 
 
 def lookup(offsets, precision: str, path: str = DEFAULT_CACHE, cell: bool = False):
-    """Cached tuning for this cluster layout (cell: the cell-list variant), or None."""
+    """Cached tuning for this cluster layout (cell: the cell-list variant), or
+    None: no entry, or a launch plan timed at another size."""
     entry = load_cache(path).get(bucket(offsets, precision, cell))
-    return None if entry is None else dict(entry["tuning"])
+    if entry is None:
+        return None
+    timed, nmax = entry.get("nmax"), _nmax(offsets)
+    if timed and not cell and not timed / SIZE_RANGE <= nmax <= timed * SIZE_RANGE:
+        return None
+    return dict(entry["tuning"])
 
 
 def main(argv=None):
@@ -125,7 +152,7 @@ def main(argv=None):
         prec = args.precision or w.precision
         best, table = tune(w, prec, args.budget)
         key = bucket(w.offsets, prec, w.rc > 0)
-        cache[key] = dict(tuning=best, ms_per_step=min(r["ms_per_step"] for r in table), workload=w.name)
+        cache[key] = dict(tuning=best, ms_per_step=pick(table)["ms_per_step"], nmax=_nmax(w.offsets), workload=w.name)
         report[w.name] = dict(key=key, best=best, table=table)
         print(json.dumps(dict(workload=w.name, key=key, best=best, ms=cache[key]["ms_per_step"])), flush=True)
     with open(args.cache, "w") as f:

@@ -121,3 +121,33 @@ for n in (3073, 3520, 3521, 3600, 4096, 4160, 4161, 4480):
         result.append([n, max(r[2] for r in records() if r[0] == "launch" and "k_sym_force" in r[1])])
 """)
     assert all(items <= 768 for _, items in got), got
+
+
+def test_auto_plans_do_not_fall_behind_the_library_s_own():
+    # a plan timed at 2243 atoms kept single clusters of 2049 to 4096 on 8
+    # wavefronts and off the symmetric sweeps; it holds near 2243 only
+    got = recorder.run("""
+result = []
+for n in (2060, 2600, 3501, 4096, 13, 147, 9000, 40000):
+    off = np.array([0, n])
+    own = []
+    for tuning in (None, "auto"):
+        with scmd.Simulation(off, cluster(n), tuning=tuning) as sim:
+            records()
+            sim.step(1)
+            own.append(sorted({tuple(r) for r in records() if r[0] == "launch"}))
+    result.append([n, own[0] == own[1]])
+""")
+    assert all(same for _, same in got), got
+
+
+def test_the_autotuner_times_the_library_s_own_plan():
+    from paper_1210_3559_amd import autotune, inputs
+    for name in ("ni147_nve", "ni2243_cooling", "batch256"):
+        assert {} in autotune.tunings(inputs.by_name(name))
+    rows = [dict(tuning={}, ms_per_step=1.0), dict(tuning=dict(pairs=3), ms_per_step=1.02),
+            dict(tuning=dict(pairs=2), ms_per_step=1.5)]
+    assert autotune.pick(rows)["tuning"] == dict(pairs=3)  # within the noise: the plan itself is recorded
+    rows[0]["ms_per_step"] = 0.5
+    assert autotune.pick(rows)["tuning"] == {}
+    assert autotune.pick([dict(tuning=dict(cell_skin=0.4), ms_per_step=1.0)])["tuning"] == dict(cell_skin=0.4)
