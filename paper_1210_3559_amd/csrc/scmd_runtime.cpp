@@ -10,6 +10,7 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <functional>
 #include <mutex>
 #include <new>
 #include <string>
@@ -227,13 +228,16 @@ int fail(scmd_ctx *c, int code, const std::string &msg) {
         return fail(ctx, SCMD_EDEVICE, "internal error");        \
     }
 
-// Row sweeps by default: single clusters up to kRowSingleMax atoms, and
-// batches of staged clusters up to kRowBatchPairsLarge unordered pairs per step
-// (kRowBatchPairs when none has more than kRowBatchSmall atoms); build_plan
-// gives the times on both sides.
+// Row sweeps by default: single clusters up to kRowSingleMax atoms; batches of
+// staged clusters up to kRowBatchPairsLarge unordered pairs per step
+// (kRowBatchPairs when none has more than kRowBatchSmall atoms), and beyond while
+// the busiest CU runs at most kRowBatchRounds rounds; build_plan gives the times on
+// both sides.
 constexpr int kRowSingleMax = 3072;
 constexpr double kRowBatchPairs = 2.5e7, kRowBatchPairsLarge = 2.5e6;
 constexpr int kRowBatchSmall = 384;
+constexpr double kRowBatchRounds = 78;
+constexpr int kComputeUnits = 256;
 
 int64_t ndof_of(int64_t n) {
     if (n >= 3) return 3 * n - 6;
@@ -456,6 +460,51 @@ int build_sym_plan(scmd_ctx *c, int target) {
     return SCMD_OK;
 }
 
+// Atoms per workgroup of a row sweep over a cluster of n atoms: wstar / n, where
+// wstar is the work (atoms times partners) each workgroup should have.
+int row_tile_atoms(int n, double wstar, int waves, bool single) {
+    const double ni_cap = std::min(64, 8 * waves);
+    int ni = n > 0 ? (int)std::min<double>(ni_cap, std::max(1.0, std::ceil(wstar / n))) : 1;
+    // a cluster of its own: at least two atoms per workgroup, whose group
+    // sums one thread each adds in a row (160 atoms 10.3 us per step with
+    // one, 9.1 with two)
+    if (single) ni = std::max(ni, std::min(2, n));
+    // each atom of a tile gets floor(groups / ni) of the 8-lane groups;
+    // when that leaves more than a tenth of the groups idle, take the
+    // largest power of two <= ni instead (it divides the group count)
+    const int groups = 8 * waves;
+    if (ni * (groups / ni) < groups - groups / 10) {
+        int p2 = 1;
+        while (2 * p2 <= ni) p2 *= 2;
+        ni = p2;
+    }
+    return ni;
+}
+
+// Rounds of the pair loop that the busiest CU of a row sweep runs: workgroups
+// start longest first, one on each CU, then the next on each.
+double row_load(const scmd_ctx *c, int target, int waves) {
+    double total = 0.0;
+    for (int k = 0; k < c->nclusters; ++k) {
+        const double n = (double)(c->offsets[k + 1] - c->offsets[k]);
+        total += n * n;
+    }
+    const double wstar = std::max(1.0, total / std::max(1, target));
+    std::vector<int> rounds;
+    for (int k = 0; k < c->nclusters; ++k) {
+        const int n = (int)(c->offsets[k + 1] - c->offsets[k]);
+        const int ni = row_tile_atoms(n, wstar, waves, c->nclusters == 1);
+        for (int t = 0; t < n; t += ni) {
+            const int streams = 8 * (8 * waves / std::min(ni, n - t));
+            rounds.push_back((n + streams - 1) / streams);
+        }
+    }
+    std::sort(rounds.begin(), rounds.end(), std::greater<int>());
+    double load = 0.0;
+    for (size_t k = 0; k < rounds.size(); k += kComputeUnits) load += rounds[k];
+    return load;
+}
+
 // Row plan: tiles of ni <= 8 * waves atoms, one workgroup each, sized so
 // that the sweep has about `target` workgroups of about equal work (ni n_c).
 int build_row_plan(scmd_ctx *c, int target, std::vector<ITile> *tiles_out) {
@@ -467,7 +516,6 @@ int build_row_plan(scmd_ctx *c, int target, std::vector<ITile> *tiles_out) {
         nmax = std::max(nmax, (int)(c->offsets[k + 1] - c->offsets[k]));
     }
     c->row_nmax = nmax;
-    const double ni_cap = std::min(64, 8 * c->row_waves);
     const double wstar = std::max(1.0, total / std::max(1, target));
     std::vector<ITile> tiles;
     int tmax = 1;
@@ -475,20 +523,7 @@ int build_row_plan(scmd_ctx *c, int target, std::vector<ITile> *tiles_out) {
         ClusterDesc &d = c->cdesc[k];
         const int off = (int)c->offsets[k];
         const int n = (int)(c->offsets[k + 1] - c->offsets[k]);
-        int ni = n > 0 ? (int)std::min<double>(ni_cap, std::max(1.0, std::ceil(wstar / n))) : 1;
-        // a cluster of its own: at least two atoms per workgroup, whose group
-        // sums one thread each adds in a row (160 atoms 10.3 us per step with
-        // one, 9.1 with two)
-        if (c->nclusters == 1) ni = std::max(ni, std::min(2, n));
-        // each atom of a tile gets floor(groups / ni) of the 8-lane groups;
-        // when that leaves more than a tenth of the groups idle, take the
-        // largest power of two <= ni instead (it divides the group count)
-        const int groups = 8 * c->row_waves;
-        if (ni * (groups / ni) < groups - groups / 10) {
-            int p2 = 1;
-            while (2 * p2 <= ni) p2 *= 2;
-            ni = p2;
-        }
+        const int ni = row_tile_atoms(n, wstar, c->row_waves, c->nclusters == 1);
         d.off = off;
         d.n = n;
         d.tile0 = (int)tiles.size();
@@ -561,17 +596,24 @@ int build_plan(scmd_ctx *c, std::vector<ITile> *tiles_out) {
         // Row sweeps evaluate every ordered pair but finish a step in two
         // launches; symmetric ones evaluate half the pairs in four launches
         // and need enough work to fill the chip.  us per step, row against
-        // symmetric: 3001 atoms 24.1 / 25.1, 3501 atoms 39 / 28; batches 4 x
-        // 2057 36.7 / 30.7, 30 x 500 26.2 / 23.2, but 100 x 300 25.3 / 28.1
-        // (a cluster of few 64-atom tiles wastes lanes and runs mostly in
-        // diagonal items).  Generic exponents have no symmetric form, and in
-        // mixed precision the symmetric coefficient rounds P_i and P_j in one
-        // order for both atoms: those keep the row sweeps wherever the
-        // clusters can be staged.
+        // symmetric: 3001 atoms 24.1 / 25.1, 3501 atoms 39 / 28.  A batch on the
+        // row sweeps takes 10.3 us and 0.16 for every round of its busiest CU
+        // (row_load), one on the symmetric sweeps 22.5 to 25 up to 4e6 pairs, so
+        // the line lies at kRowBatchRounds: 8 x 800 (50 rounds) 18.5 / 22.5, 8 x
+        // 1000 (63) 20.4 / 23.3, 3 x 1700 (71) 22.3 / 25.3, but 13 x 700 (88)
+        // 24.4 / 22.9, 3 x 1500 (94) 25.5 / 23.1, 38 x 400 (100) 26.4 / 23.7, 4 x
+        // 2057 35.5 / 30.7.  Clusters of few 64-atom tiles waste symmetric lanes
+        // and run mostly in diagonal items: 100 x 300 24.7 / 28.6, 60 x 384 27.2 /
+        // 27.8 (but 100 x 384 39.7 / 35.3).  Generic exponents have no symmetric
+        // form, and in mixed precision the symmetric coefficient rounds P_i and
+        // P_j in one order for both atoms: those keep the row sweeps wherever
+        // the clusters can be staged.
         const bool wide = c->pc.generic || c->precision == SCMD_MIXED;
+        const int row_target = c->tuning.target_items > 0 ? c->tuning.target_items : 256;
         const bool row_single = nmax <= (wide ? kRowStageMax : kRowSingleMax);
         const bool row_batch = nmax <= kRowStageMax &&
-                               upairs <= (wide || nmax <= kRowBatchSmall ? kRowBatchPairs : kRowBatchPairsLarge);
+                               (upairs <= (wide || nmax <= kRowBatchSmall ? kRowBatchPairs : kRowBatchPairsLarge) ||
+                                (upairs <= kRowBatchPairs && row_load(c, row_target, 8) <= kRowBatchRounds));
         const bool row_default = !shape_given && (batch ? row_batch : row_single);
         if (c->neighbour == SCMD_ALLPAIRS && (c->tuning.pairs == 3 || (c->tuning.pairs == 0 && row_default))) {
             c->sym = false;
@@ -587,7 +629,7 @@ int build_plan(scmd_ctx *c, std::vector<ITile> *tiles_out) {
             // 17.7 / 18.2); row sweeps asked for have 8 unless told otherwise
             c->row_waves = c->tuning.waves_j > 0 ? c->tuning.waves_j
                                                  : batch || c->tuning.pairs == 3 || nmax <= 2560 ? 8 : 16;
-            return build_row_plan(c, c->tuning.target_items > 0 ? c->tuning.target_items : 256, tiles_out);
+            return build_row_plan(c, row_target, tiles_out);
         }
         c->sym = allowed && (c->tuning.pairs == 2 ||
                              (c->tuning.pairs == 0 && (batch || nmax > (shape_given ? kRowStageMax : kRowSingleMax))));

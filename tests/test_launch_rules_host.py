@@ -151,3 +151,19 @@ def test_the_autotuner_times_the_library_s_own_plan():
     rows[0]["ms_per_step"] = 0.5
     assert autotune.pick(rows)["tuning"] == {}
     assert autotune.pick([dict(tuning=dict(cell_skin=0.4), ms_per_step=1.0)])["tuning"] == dict(cell_skin=0.4)
+
+
+def test_middle_batches_take_the_sweeps_that_are_faster():
+    # the batches that the row sweeps run faster (us per step against symmetric)
+    # and those they do not, at alike numbers of pairs
+    got = recorder.run("""
+result = []
+for sizes in ([800] * 8, [1000] * 6, [1000] * 8, [1300] * 4, [1700] * 3, [2000] * 2, [500] * 27, [400] * 42,
+              [2243] + [55] * 20, [1500] * 3, [1400] * 4, [700] * 13, [400] * 38, [1000] * 10, [2400] * 2, [2057] * 4):
+    off = np.concatenate([[0], np.cumsum(sizes)])
+    with scmd.Simulation(off, np.concatenate([cluster(n) for n in sizes])) as sim:
+        records()
+        sim.step(1)
+        result.append([sizes[0], len(sizes), any("k_row" in r[1] for r in records())])
+""")
+    assert [row for *_, row in got] == [True] * 9 + [False] * 7, got
