@@ -233,7 +233,7 @@ int fail(scmd_ctx *c, int code, const std::string &msg) {
 // (kRowBatchPairs when none has more than kRowBatchSmall atoms), and beyond while
 // the busiest CU runs at most kRowBatchRounds rounds; build_plan gives the times on
 // both sides.
-constexpr int kRowSingleMax = 3072;
+constexpr int kRowSingleMax = 3520;
 constexpr double kRowBatchPairs = 2.5e7, kRowBatchPairsLarge = 2.5e6;
 constexpr int kRowBatchSmall = 384;
 constexpr double kRowBatchRounds = 78;
@@ -596,8 +596,8 @@ int build_plan(scmd_ctx *c, std::vector<ITile> *tiles_out) {
         // Row sweeps evaluate every ordered pair but finish a step in two
         // launches; symmetric ones evaluate half the pairs in four launches
         // and need enough work to fill the chip.  us per step, row against
-        // symmetric: 3001 atoms 24.1 / 25.1, 3501 atoms 39 / 28.  A batch on the
-        // row sweeps takes 10.3 us and 0.16 for every round of its busiest CU
+        // symmetric: 3001 atoms 23.3 / 26.5, 3328 26.6 / 27.7, 3520 27.8 / 27.9,
+        // 3600 29.7 / 29.1, 4000 31.9 / 30.5.  A batch on the row sweeps takes 10.3 us and 0.16 for every round of its busiest CU
         // (row_load), one on the symmetric sweeps 22.5 to 25 up to 4e6 pairs, so
         // the line lies at kRowBatchRounds: 8 x 800 (50 rounds) 18.5 / 22.5, 8 x
         // 1000 (63) 20.4 / 23.3, 3 x 1700 (71) 22.3 / 25.3, but 13 x 700 (88)

@@ -116,7 +116,7 @@ def test_symmetric_items_of_middle_sizes_fit_three_per_compute_unit():
     got = recorder.run("""
 result = []
 for n in (3073, 3520, 3521, 3600, 4096, 4160, 4161, 4480):
-    with scmd.Simulation([0, n], cluster(n)) as sim:
+    with scmd.Simulation([0, n], cluster(n), tuning=dict(pairs=2)) as sim:
         sim.compute()
         result.append([n, max(r[2] for r in records() if r[0] == "launch" and "k_sym_force" in r[1])])
 """)
@@ -167,3 +167,16 @@ for sizes in ([800] * 8, [1000] * 6, [1000] * 8, [1300] * 4, [1700] * 3, [2000] 
         result.append([sizes[0], len(sizes), any("k_row" in r[1] for r in records())])
 """)
     assert [row for *_, row in got] == [True] * 9 + [False] * 7, got
+
+
+def test_single_clusters_change_sweeps_where_both_take_as_long():
+    got = recorder.run("""
+result = []
+for precision in ("fp64", "mixed"):
+    for n in (3072, 3073, 3520, 3521, 4096, 4097):
+        with scmd.Simulation([0, n], cluster(n), precision=precision) as sim:
+            records()
+            sim.step(1)
+            result.append(any("k_row" in r[1] for r in records()))
+""")
+    assert got == [True, True, True, False, False, False, True, True, True, True, True, False]
