@@ -269,10 +269,13 @@ hipError_t launch_bath_prep(const StepArgs &a, const int32_t *atom_cluster, cons
 // kResidentFew the sweeps are faster until a batch has the pairs of about 43
 // clusters as large as its largest (kResidentPairs n^2): 16 of 190 10.3 / 13.5, 40:
 // 13.0 / 13.5, 48: 14.4 / 13.5, 64: 15.2 / 13.4; one of 190 with 511 of 55 18.3 /
-// 13.5.  kResidentMax is what one CU's LDS holds.
+// 13.5.  General exponents take one CU longer: 96 atoms 9.2 / 7.9, 104: 9.4 / 9.0,
+// 110: 9.3 / 10.5 (mixed 9.2 / 11.1), 147: 9.5 / 14.9; 64 clusters of 152 16.6 /
+// 15.5, 44 of 190 18.7 / 20.6 (mixed 16.0 / 22.4), 64: 20.2 / 20.3, 100: 28.4 / 20.5.
+// kResidentMax is what one CU's LDS holds.
 constexpr int kResidentMax = 190;
-constexpr int kResidentFew = 152;
-constexpr double kResidentPairs = 21.0;
+constexpr int kResidentFew = 152, kResidentFewGeneric = 96;
+constexpr double kResidentPairs = 21.0, kResidentPairsGeneric = 35.0;
 hipError_t launch_resident(const SweepBuffers &B, const StepArgs &a, int nclusters, int nmax, int nsteps,
                            const PotConst &pc, int precision, hipStream_t s);
 

@@ -619,9 +619,10 @@ int build_plan(scmd_ctx *c, std::vector<ITile> *tiles_out) {
             c->sym = false;
             c->row = true;
             // (kResidentMax: both sides measured)
+            const double fill = (c->pc.generic ? kResidentPairsGeneric : kResidentPairs) * (double)nmax * (double)nmax;
             c->resident = c->tuning.pairs == 0 && c->natoms > 0 &&
-                          (nmax <= kResidentFew ||
-                           (nmax <= kResidentMax && upairs >= kResidentPairs * (double)nmax * (double)nmax));
+                          (nmax <= (c->pc.generic ? kResidentFewGeneric : kResidentFew) ||
+                           (nmax <= kResidentMax && upairs >= fill));
             // one workgroup per CU from about 2560 atoms on (two no longer fit
             // the LDS), so the runs have to divide the groups evenly: 16
             // wavefronts do where 8 leave a fifth of them idle or need a

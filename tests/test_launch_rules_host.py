@@ -180,3 +180,18 @@ for precision in ("fp64", "mixed"):
             result.append(any("k_row" in r[1] for r in records()))
 """)
     assert got == [True, True, True, False, False, False, True, True, True, True, True, False]
+
+
+def test_general_exponents_leave_the_resident_kernel_earlier():
+    # the power chains take one CU longer: 147 atoms 14.9 us per step, row sweeps 9.5
+    got = recorder.run("""
+result = []
+for precision in ("fp64", "mixed"):
+    for n, k in ((96, 1), (97, 1), (152, 1), (152, 32), (190, 64), (190, 72), (152, 72)):
+        with scmd.Simulation(np.arange(k + 1) * n, np.tile(cluster(n), (k, 1)), precision=precision,
+                             params=dict(n=12, m=6, c=144.41)) as sim:
+            records()
+            sim.step(1)
+            result.append(any("k_resident" in r[1] for r in records()))
+""")
+    assert got == 2 * [True, False, False, False, False, True, True]

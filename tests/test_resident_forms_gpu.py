@@ -62,8 +62,10 @@ LAN = dict(kind="langevin", T_start=900.0, T_end=600.0, ramp_steps=10, gamma=10.
 @pytest.mark.parametrize("n,copies,bath", [(13, 1, None), (48, 1, LAN), (49, 1, None), (96, 1, LAN), (97, 1, None),
                                            (152, 1, LAN), (190, 44, None)])
 def test_every_form_follows_the_oracle(n, copies, bath, precision, exponents):
-    # 44 copies: from 153 atoms on clusters are resident in batches that fill the chip
+    # larger clusters are resident in batches that fill the chip
     params = PARAMS[exponents]
+    if n > 96 and params:
+        copies = 72
     p, v = _cluster(n, 70)
     print(f"[resident] n={n} x {copies} {precision} {exponents}", flush=True)
     with scmd.Simulation(np.arange(copies + 1) * n, np.tile(p, (copies, 1)), np.tile(v, (copies, 1)), dt=1.0,
