@@ -85,7 +85,6 @@ __global__ __launch_bounds__(kSelBlock) void k_rdf_select(const double4 *__restr
 }
 
 constexpr int kHistBlock = 256;
-constexpr int kHistGroups = 1024;  // workgroups, while a workgroup's 32-bit bins hold all their pairs
 
 // Workgroup b takes the reference atoms b, b + gridDim.x, ... against every
 // atom of the cluster; counts go to a workgroup histogram in LDS, then to the
@@ -94,7 +93,8 @@ constexpr int kHistGroups = 1024;  // workgroups, while a workgroup's 32-bit bin
 // within 10 A: 8 per workgroup on 48 CUs took 24 us); with many references each
 // workgroup takes several, so the flush stays small.  The bin is
 // floor(d / dr) of the IEEE quotient: the product with 1 / dr decides it unless
-// it comes within rounding of an integer, where the division is done.
+// it comes within rounding of an integer, where the division is done (all of 48,077
+// atoms, 100 bins: 3.8 ms dividing always, 3.4 so).
 __global__ __launch_bounds__(kHistBlock) void k_rdf_hist(const double4 *__restrict__ rp, int off, int n,
                                                         const int32_t *__restrict__ refs,
                                                         const int *__restrict__ nref, double dr, int nbins,
@@ -114,10 +114,14 @@ __global__ __launch_bounds__(kHistBlock) void k_rdf_hist(const double4 *__restri
             if (j == i) continue;
             const double4 qj = rp[off + j];
             const double dx = qi.x - qj.x, dy = qi.y - qj.y, dz = qi.z - qj.z;
-            const double d = sqrt(dx * dx + dy * dy + dz * dz);
+            double d = sqrt(dx * dx + dy * dy + dz * dz);
             const double q = d * inv_dr;
+            double b = floor(q);
             // (also an infinite or subnormal 1 / dr, and NaN, go to the division)
-            const double b = fabs(q - rint(q)) > 1.0e-12 * q + 1.0e-290 && q < 1.0e300 ? floor(q) : floor(d / dr);
+            if (!(fabs(q - rint(q)) > 1.0e-12 * q + 1.0e-290 && q < 1.0e300)) {
+                asm volatile("" : "+v"(d));  // a branch: as a select the division would be done for every pair
+                b = floor(d / dr);
+            }
             if (b < end) atomicAdd(&hist[(int)b], 1u);
         }
     }
@@ -379,13 +383,20 @@ hipError_t launch_rdf(const double4 *rp, int off, int n, double r_select, double
     if (n > 0) {
         const size_t lds = (size_t)nbins * sizeof(unsigned int);
         if (hipError_t e = allow_lds(k_rdf_hist, lds, kRdfMaxBins * sizeof(unsigned int)); e != hipSuccess) return e;
-        // Every reference may add n - 1 pairs to one bin: from 2,097,153 atoms
-        // on, 1024 workgroups no longer share out the references finely enough.
-        // Workgroups beyond the references return at once.
+        // Enough workgroups to fill the chip (four per CU, or what the bins leave
+        // room for), few enough that clearing and flushing the bins stays small:
+        // 1000 atoms with 32,768 bins 113 us at 1024 workgroups, 71 at 256.  With
+        // many references eight for each workgroup, for the balance (all of
+        // 48,077 atoms, 100 bins: 5.1 ms at 1024 workgroups, 4.3 at 6010), unless the
+        // bins fill the LDS (32,768 bins: 10.4 ms at 256, 10.6 at 6010).  And every
+        // reference may add n - 1 pairs to one 32-bit bin, which asks for more
+        // workgroups of large clusters.  Those beyond the references return at once.
+        const int fill = kComputeUnits * (lds * 4 <= kLdsBytes ? 4 : (int)(kLdsBytes / lds));
+        unsigned groups = n < fill ? n : fill;
+        if (n >= nbins && lds * 2 <= kLdsBytes) groups = max(groups, (unsigned)(n + 7) / 8);
         const unsigned most = 0xFFFFFFFFu / (unsigned)(n > 1 ? n - 1 : 1);  // references per workgroup
-        const unsigned groups = (unsigned)(n - 1) / most + 1;
-        const unsigned usual = n < kHistGroups ? n : kHistGroups;
-        hipLaunchKernelGGL(k_rdf_hist, dim3(groups > usual ? groups : usual), dim3(kHistBlock), lds, s, rp, off, n,
+        groups = max(groups, (unsigned)(n - 1) / most + 1);
+        hipLaunchKernelGGL(k_rdf_hist, dim3(groups), dim3(kHistBlock), lds, s, rp, off, n,
                            refs, nref, dr, nbins, counts);
     }
     if (nref_total) hipLaunchKernelGGL(k_add_nref, dim3(1), dim3(64), 0, s, nref, nref_total);

@@ -11,6 +11,9 @@ namespace scmd {
 constexpr double kEvPerUA2Fs2 = 103.64269652680505;
 constexpr double kBoltzmannEv = 8.617333262145179e-05;
 
+constexpr int kComputeUnits = 256;
+constexpr size_t kLdsBytes = 160 * 1024;  // of a compute unit
+
 // Sentinel coordinates for lanes/atoms past the end of a tile.  Atom slots
 // past the owned range sit at -kFar, j slots past a chunk at +kFar, so every
 // pair touching a sentinel has r^2 ~ 1e301: all its power terms underflow to

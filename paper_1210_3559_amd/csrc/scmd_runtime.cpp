@@ -237,7 +237,6 @@ constexpr int kRowSingleMax = 3520;
 constexpr double kRowBatchPairs = 2.5e7, kRowBatchPairsLarge = 2.5e6;
 constexpr int kRowBatchSmall = 384;
 constexpr double kRowBatchRounds = 78;
-constexpr int kComputeUnits = 256;
 
 int64_t ndof_of(int64_t n) {
     if (n >= 3) return 3 * n - 6;

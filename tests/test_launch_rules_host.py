@@ -18,7 +18,6 @@ for n in (1, 2, 1000, 1024, 1025, 48077, 2097152, 2097153, 3000000, 6000000):
     for n, groups in got:
         per_group = -(-n // groups)
         assert per_group * (n - 1) < 2**32, (n, groups)
-    assert dict(map(tuple, got))[48077] == 1024
 
 
 def test_an_evaluation_takes_the_kernels_of_the_run():
@@ -195,3 +194,21 @@ for precision in ("fp64", "mixed"):
             result.append(any("k_resident" in r[1] for r in records()))
 """)
     assert got == 2 * [True, False, False, False, False, True, True]
+
+
+def test_histogram_workgroups_follow_the_bins_and_the_references():
+    # (atoms, bins, workgroups): one per atom, four per CU, what the LDS leaves room
+    # for, eight references each
+    want = [(100, 400, 100), (2057, 400, 1024), (1000, 20000, 512), (1000, 32768, 256), (48077, 400, 6010),
+            (48077, 20000, 6010), (48077, 32768, 256)]
+    got = recorder.run(f"""
+result = []
+for n, bins, _ in {want!r}:
+    pos = np.zeros((n, 3))
+    pos[:, 0] = np.arange(n)
+    with scmd.Simulation([0, n], pos) as sim:
+        records()
+        sim.rdf(0, 1.0, bins)
+        result.append([n, bins] + [r[2] for r in records() if r[0] == "launch" and "k_rdf_hist" in r[1]])
+""")
+    assert list(map(tuple, got)) == want
