@@ -212,3 +212,25 @@ for n, bins, _ in {want!r}:
         result.append([n, bins] + [r[2] for r in records() if r[0] == "launch" and "k_rdf_hist" in r[1]])
 """)
     assert list(map(tuple, got)) == want
+
+
+def test_getters_pack_once_where_the_staging_area_holds_the_result():
+    # results that fit half the staging area, all of it, and neither; densities of
+    # more than 16 KiB are copied without a kernel
+    got = recorder.run("""
+result = []
+for n in (1, 2048, 2049, 5461, 5462, 10922, 10923, 40000):
+    pos = np.zeros((n, 3))
+    pos[:, 0] = np.arange(n)
+    with scmd.Simulation([0, n], pos, rc=8.8) as sim:
+        sim.compute()
+        records()
+        launches = []
+        for get in (sim.positions, sim.density):
+            get()
+            launches.append(len([r for r in records() if r[0] == "launch"]))
+        result.append([n] + launches)
+""")
+    for n, xyz, density in got:
+        assert xyz == (1 if 24 * n <= 1 << 18 else -(-n // ((1 << 17) // 24))), n
+        assert density == (1 if n <= 2048 else 0), n
