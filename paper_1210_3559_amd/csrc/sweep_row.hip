@@ -321,17 +321,27 @@ __global__ __launch_bounds__(64 * W) void k_row_density(RowArgs ra, DensityOut o
         qi = src[i_local];
         row_loop(L, src, rt.n, i_local, pair, quad, 0, L.k_end);
     }
-    if constexpr (PREC == SCMD_FP64 && !GEN) {
-        // a product of four r^2 left the range (density_terms): pair by pair
-        if (!isfinite(acc)) {
-            acc = 0.0;
-            for (int j = L.s; j < rt.n; j += L.S) pair(src[j], j == i_local);
-        }
-    }
     double v[1] = {acc};
     row_reduce<W, 1>(L, v, sh);
     double emb = 0.0;
-    if (tid < L.ni) emb = density_atom_at(rt.i0 + tid, v[0], src[rt.i0 - rt.off + tid], o, pc);
+    if (tid < L.ni) {
+        const int own = rt.i0 - rt.off + tid;
+        const double4 q = src[own];
+        double u6 = v[0];
+        if constexpr (PREC == SCMD_FP64 && !GEN) {
+            // a product of four r^2 left the range (density_terms): pair by pair
+            if (!isfinite(u6)) {
+                u6 = 0.0;
+                for (int j = 0; j < rt.n; ++j) {
+                    const double4 a = src[j];
+                    const double dx = q.x - a.x, dy = q.y - a.y, dz = q.z - a.z;
+                    if (j != own)
+                        u6 += density_term<PREC, GEN>(__builtin_fma(dx, dx, __builtin_fma(dy, dy, dz * dz)), pc);
+                }
+            }
+        }
+        emb = density_atom_at(rt.i0 + tid, u6, q, o, pc);
+    }
     if (tid < 64) {
         emb = wave_sum(emb);
         if (tid == 0) o.tile_sums[(size_t)rt.tix * kTileSums + 0] = emb;
