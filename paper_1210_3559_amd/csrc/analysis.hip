@@ -185,7 +185,10 @@ __device__ void block_sum(double (&v)[K], double *sh) {
 
 // 1/x and 1/sqrt(x) from the hardware estimates and two Newton steps (a few
 // 2^-53): one thread works through a chain of these in the eigenproblem, where
-// library division and roots cost several times the latency.
+// library division and roots cost several times the latency (a histogram and a
+// coefficient of 2057 atoms 87.6 us with these, 93.1 with division and root).  The
+// coefficient is no further from 80-bit arithmetic for it: mean relative error over
+// 1512 windows of 13 to 1000 atoms 7.06e-16, with division and root 7.11e-16.
 __device__ __forceinline__ double rcp2(double x) {
     double y = __builtin_amdgcn_rcp(x);
     y = __builtin_fma(y, __builtin_fma(-x, y, 1.0), y);

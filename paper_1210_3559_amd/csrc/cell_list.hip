@@ -344,7 +344,7 @@ __device__ __forceinline__ void cell_scan(const int *__restrict__ count, int tot
 }
 
 // The scan as a launch of its own, for grids of more than kScanLds cells (100
-// clusters of 2243 atoms: 385 us per step, 684 when rebuilt every step).
+// clusters of 2243 atoms: 351 us per step, 676 when rebuilt every step).
 __global__ __launch_bounds__(kScanBlock) void k_cell_scan(const int *__restrict__ count, int *__restrict__ start,
                                                           int *__restrict__ corder, int total,
                                                           const int *__restrict__ flag) {
@@ -356,11 +356,11 @@ __global__ __launch_bounds__(kScanBlock) void k_cell_scan(const int *__restrict_
 // its cell (which slot depends on timing; k_cell_order ranks them).  SCAN: every
 // workgroup scans the counts for itself, the first one stores the result, while
 // the starts fit the LDS of two workgroups per CU (kScanLds).  A launch of its own
-// for the scan costs 4.7 us on every step, with or without a build, and bounds it:
-// us per step without and with SCAN, lists reused | rebuilt every step, 500 atoms
-// 32.8 -> 31.4 | 44.0 -> 43.3, 48,077 atoms 87.6 -> 85.3 | 129.4 -> 126.1, 98
-// clusters of 13 atoms (12,250 cells) 46.3 -> 43.6 | 73.3 -> 63.3.  Every launch
-// leaves the boxes reset for the next check.
+// for the scan costs 1.3 us on every step, with or without a build: us per step
+// without and with SCAN, lists reused | rebuilt every step, 500 atoms 29.9 -> 28.5 |
+// 43.0 -> 41.8, 48,077 atoms 81.9 -> 80.4 | 127.5 -> 126.1, 98 clusters of 13 atoms
+// (12,250 cells) 26.9 -> 25.4 | 47.3 -> 46.0.  Every launch leaves the boxes reset
+// for the next check.
 template <bool SCAN>
 __global__ __launch_bounds__(kScanBlock) void k_cell_scatter(const int *__restrict__ count, int *__restrict__ start,
                                                              int *__restrict__ corder, int total,

@@ -2,18 +2,18 @@
 // any number of steps in one launch, the cluster held in registers and LDS.
 //
 // A step of a small cluster on the row sweeps is two launches that each last
-// little longer than an empty one (Ni147: 5.1 + 5.5 us, a 3.3 us floor per
-// launch): nothing is gained by spreading 10,731 pairs over 256 CUs.  Here one
-// CU does all of them and a barrier takes the place of a launch.  That CU's
-// FP64 rate is then the bound, so every unordered pair is evaluated once:
-// S neighbouring lanes work for atom i; lane s meets the atoms i + k (mod n) of
-// the offsets k = 1 + s, 1 + s + S, ... <= (n - 1) / 2, adds the term to its own
-// sum and leaves it in LDS for the other (row k, its atom), and after a barrier
-// it collects what the pairs (i - k, i) left.  For even n the offset n / 2 meets every pair
-// from both ends.  Positions are stored twice in a row, so i + k never wraps;
-// the S lanes add their sums with DPP and all of them carry the atom's state.
-// Everything is in a fixed order: results do not depend on how a run is cut
-// into launches.  kResidentMax gives the times.
+// little longer than an empty one (Ni147: 9.6 us, a 3.3 us floor per launch):
+// nothing is gained by spreading 10,731 pairs over 256 CUs.  Here one CU does all of
+// them and a barrier takes the place of a launch.  That CU's FP64 rate is then the
+// bound, so every unordered pair is evaluated once: S neighbouring lanes work for
+// atom i; lane s meets the atoms i + k (mod n) of the offsets k = 1 + s, 1 + s + S,
+// ... <= (n - 1) / 2, adds the term to its own sum and leaves it in LDS for the other
+// (row k, its atom), and after a barrier it collects what the pairs (i - k, i) left.
+// For even n the offset n / 2 meets every pair from both ends.  Positions are stored
+// twice in a row, so i + k never wraps; the S lanes add their sums with DPP and all
+// of them carry the atom's state.  Everything is in a fixed order: results do not
+// depend on how a run is cut into launches, nor on evaluations between its calls,
+// which run here too.  kResidentMax gives the times.
 //
 // The scheme is the paper's (Sec. 2 "Computational approach": the densities of
 // Eq. (rho), then the forces of Eq. (SC), velocity-Verlet or the Langevin bath).
