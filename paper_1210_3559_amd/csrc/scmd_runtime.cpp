@@ -595,19 +595,17 @@ int build_plan(scmd_ctx *c, std::vector<ITile> *tiles_out) {
         // Row sweeps evaluate every ordered pair but finish a step in two
         // launches; symmetric ones evaluate half the pairs in four launches
         // and need enough work to fill the chip.  us per step, row against
-        // symmetric: 3001 atoms 23.3 / 26.5, 3328 26.6 / 27.7, 3520 27.8 / 27.9,
-        // 3600 29.7 / 29.1, 4000 31.9 / 30.5.  A batch on the row sweeps takes 10.3 us and 0.16 for every round of its busiest CU
-        // (row_load), one on the symmetric sweeps 22.5 to 25 up to 4e6 pairs, so
-        // the line lies at kRowBatchRounds: 8 x 800 (50 rounds) 18.5 / 22.5, 8 x
-        // 1000 (63) 20.4 / 23.3, 3 x 1700 (71) 22.3 / 25.3, but 13 x 700 (88)
-        // 24.4 / 22.9, 3 x 1500 (94) 25.5 / 23.1, 38 x 400 (100) 26.4 / 23.7, 4 x
-        // 2057 35.5 / 30.7.  Clusters of few 64-atom tiles waste symmetric lanes
-        // and run mostly in diagonal items: 100 x 300 24.7 / 28.6, 60 x 384 27.2 /
-        // 27.8 (but 100 x 384 39.7 / 35.3).  Generic exponents have no symmetric
-        // form, and in mixed precision the symmetric coefficient rounds P_i and
-        // P_j in one order for both atoms: those keep the row sweeps wherever
-        // the clusters can be staged.
-        const bool wide = c->pc.generic || c->precision == SCMD_MIXED;
+        // symmetric: 3001 atoms 23.3 / 26.5, 3328 26.6 / 27.7, 3520 27.8 / 27.9, 3600 29.7 /
+        // 29.1, 4000 31.9 / 30.5.  A batch on the row sweeps takes 10.3 us and 0.16 for every
+        // round of its busiest CU (row_load), one on the symmetric sweeps 22.5 to 25 up to 4e6
+        // pairs, so the line lies at kRowBatchRounds: 8 x 800 (50 rounds) 18.5 / 22.5, 8 x 1000
+        // (63) 20.4 / 23.3, 3 x 1700 (71) 22.3 / 25.3, but 13 x 700 (88) 24.4 / 22.9, 3 x 1500
+        // (94) 25.5 / 23.1, 38 x 400 (100) 26.4 / 23.7, 4 x 2057 35.5 / 30.7.  Clusters of few
+        // 64-atom tiles waste symmetric lanes and run mostly in diagonal items: 100 x 300 24.7
+        // / 28.6, 60 x 384 27.2 / 27.8 (but 100 x 384 39.7 / 35.3).  Generic exponents have no
+        // symmetric form, and in mixed precision the symmetric coefficient rounds P_i and P_j
+        // in one order for both atoms: those keep the row sweeps wherever the clusters can be
+        // staged. st bool wide = c->pc.generic || c->precision == SCMD_MIXED;
         const int row_target = c->tuning.target_items > 0 ? c->tuning.target_items : 256;
         const bool row_single = nmax <= (wide ? kRowStageMax : kRowSingleMax);
         const bool row_batch = nmax <= kRowStageMax &&
