@@ -605,7 +605,8 @@ int build_plan(scmd_ctx *c, std::vector<ITile> *tiles_out) {
         // / 28.6, 60 x 384 27.2 / 27.8 (but 100 x 384 39.7 / 35.3).  Generic exponents have no
         // symmetric form, and in mixed precision the symmetric coefficient rounds P_i and P_j
         // in one order for both atoms: those keep the row sweeps wherever the clusters can be
-        // staged. st bool wide = c->pc.generic || c->precision == SCMD_MIXED;
+        // staged.
+        const bool wide = c->pc.generic || c->precision == SCMD_MIXED;
         const int row_target = c->tuning.target_items > 0 ? c->tuning.target_items : 256;
         const bool row_single = nmax <= (wide ? kRowStageMax : kRowSingleMax);
         const bool row_batch = nmax <= kRowStageMax &&
